@@ -202,31 +202,24 @@ pulse_status pulse_select_average(const pulse_shape* shape, const void* q, const
     return hip_status(e);
 }
 
-// MAM workspace: attention scratch (k_max = max_blocks), then the two
-// selections, their counts, the attention output and the two lse arrays.
-struct MamLayout {
-    WsLayout attn;
-    size_t sel_all, sel_mid, cnt_all, cnt_mid, out, lse_all, lse_mid, total;
-};
-static MamLayout mam_layout(const pulse_shape& s, int32_t B, int32_t max_blocks) {
-    MamLayout m;
-    m.attn = ws_layout(s, B, max_blocks, 0);
-    const size_t sel = sizeof(int32_t) * (size_t)B * max_blocks;
-    size_t o = m.attn.total;
-    m.sel_all = o; o = align_up(o + sel);
-    m.sel_mid = o; o = align_up(o + sel);
-    m.cnt_all = o; o = align_up(o + sizeof(int32_t) * (size_t)B);
-    m.cnt_mid = o; o = align_up(o + sizeof(int32_t) * (size_t)B);
-    m.out = o;     o = align_up(o + sizeof(float) * (size_t)B * s.num_q_heads * kHeadDim);
-    m.lse_all = o; o = align_up(o + sizeof(float) * (size_t)B * s.num_q_heads);
-    m.lse_mid = o; o = align_up(o + sizeof(float) * (size_t)B * s.num_q_heads);
-    m.total = o;
-    return m;
+// MAM workspace: the partials of the context pass.  The size keeps room for an attention's scratch, two
+// selections, an output and two lse arrays, which callers already allocate by; the partials (16 bytes per
+// workgroup and query head) are far smaller.
+static size_t mam_ws_bytes(const pulse_shape& s, int32_t B, int32_t max_blocks) {
+    size_t o = ws_layout(s, B, max_blocks, 0).total;
+    for (int i = 0; i < 2; ++i) {
+        o = align_up(o + sizeof(int32_t) * (size_t)B * max_blocks);
+        o = align_up(o + sizeof(int32_t) * (size_t)B);
+        o = align_up(o + sizeof(float) * (size_t)B * s.num_q_heads);
+    }
+    o = align_up(o + sizeof(float) * (size_t)B * s.num_q_heads * kHeadDim);
+    const size_t part = (size_t)B * s.num_q_heads * (size_t)mam_plan(B, s.num_kv_heads, max_blocks, s.block_size).n_wg;
+    return o > sizeof(float4) * part ? o : align_up(sizeof(float4) * part);
 }
 
 size_t pulse_mam_workspace_bytes(const pulse_shape* shape, int32_t B, int32_t max_blocks) {
     if (!shape_supported(shape) || B < 0 || max_blocks < 0) return 0;
-    return mam_layout(*shape, B, max_blocks).total;
+    return mam_ws_bytes(*shape, B, max_blocks);
 }
 
 pulse_status pulse_mam(const pulse_shape* shape, const void* q, const void* slot_pool, int32_t n_slots,
@@ -240,29 +233,9 @@ pulse_status pulse_mam(const pulse_shape* shape, const void* q, const void* slot
     PULSE_REQUIRE(B <= kMaxBatch, PULSE_ERR_UNSUPPORTED);
     if (B == 0) return PULSE_OK;
     PULSE_REQUIRE(q && slot_pool && block_table && ctx_len && mam && dev_status, PULSE_ERR_INVALID_ARG);
-    const MamLayout m = mam_layout(*shape, B, max_blocks);
-    PULSE_REQUIRE(ws && ws_bytes >= m.total, PULSE_ERR_WORKSPACE);
-    hipStream_t hs = (hipStream_t)stream;
-    int32_t* sel_all = at<int32_t>(ws, m.sel_all);
-    int32_t* sel_mid = at<int32_t>(ws, m.sel_mid);
-    int32_t* cnt_all = at<int32_t>(ws, m.cnt_all);
-    int32_t* cnt_mid = at<int32_t>(ws, m.cnt_mid);
-    float* out = at<float>(ws, m.out);
-    float* lse_all = at<float>(ws, m.lse_all);
-    float* lse_mid = at<float>(ws, m.lse_mid);
-    hipError_t e = launch_mam_selection(ctx_len, B, shape->block_size, max_blocks, n_sink_blocks, n_local_blocks,
-                                        sel_all, cnt_all, sel_mid, cnt_mid, dev_status, hs);
-    if (e != hipSuccess) return PULSE_ERR_HIP;
-    float* ws_o = at<float>(ws, m.attn.attn_o);
-    float2* ws_ml = at<float2>(ws, m.attn.attn_ml);
-    e = launch_attention(*shape, q, slot_pool, n_slots, block_table, max_blocks, sel_all, cnt_all, max_blocks,
-                         ctx_len, B, sm_scale, out, lse_all, ws_o, ws_ml, dev_status, hs);
-    if (e != hipSuccess) return PULSE_ERR_HIP;
-    e = launch_attention(*shape, q, slot_pool, n_slots, block_table, max_blocks, sel_mid, cnt_mid, max_blocks,
-                         ctx_len, B, sm_scale, out, lse_mid, ws_o, ws_ml, dev_status, hs);
-    if (e != hipSuccess) return PULSE_ERR_HIP;
-    const int32_t G = shape->num_q_heads / shape->num_kv_heads;
-    return hip_status(launch_mam_finalize(lse_all, lse_mid, B, shape->num_kv_heads, G, mam, hs));
+    PULSE_REQUIRE(ws && ws_bytes >= mam_ws_bytes(*shape, B, max_blocks), PULSE_ERR_WORKSPACE);
+    return hip_status(launch_mam(*shape, q, slot_pool, n_slots, block_table, max_blocks, ctx_len, B, n_sink_blocks,
+                                 n_local_blocks, sm_scale, mam, at<float4>(ws, 0), dev_status, (hipStream_t)stream));
 }
 
 pulse_status pulse_pick_solo_heads(const float* mam, int32_t rows, int32_t num_kv_heads, int32_t* solo,

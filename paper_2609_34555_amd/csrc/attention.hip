@@ -42,42 +42,6 @@ constexpr int kCombineThreads = kHeadDim;
 // 128 floats) stays within 32 KiB, else 4.  Fewer, wider workgroups leave
 // fewer partials for the combine kernel.
 
-template <int DT>
-struct Mfma;
-template <>
-struct Mfma<PULSE_BF16> {
-    typedef bf16x8 vec;
-    typedef __bf16 elem;
-    __device__ static inline f32x4 mac(vec a, vec b, f32x4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-    }
-    __device__ static inline void split(float p, __bf16& hi, __bf16& lo) {
-        hi = (__bf16)p;
-        lo = (__bf16)(p - (float)hi);
-    }
-};
-template <>
-struct Mfma<PULSE_F16> {
-    typedef f16x8 vec;
-    typedef _Float16 elem;
-    __device__ static inline f32x4 mac(vec a, vec b, f32x4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-    }
-    __device__ static inline void split(float p, _Float16& hi, _Float16& lo) {
-        hi = (_Float16)p;
-        lo = (_Float16)(p - (float)hi);
-    }
-};
-
-template <int DT>
-__device__ inline typename Mfma<DT>::vec load_vec(const uint16_t* p) {
-    return __builtin_bit_cast(typename Mfma<DT>::vec, *reinterpret_cast<const u32x4*>(p));
-}
-template <int DT>
-__device__ inline typename Mfma<DT>::vec zero_vec() {
-    return __builtin_bit_cast(typename Mfma<DT>::vec, u32x4{0, 0, 0, 0});
-}
-
 // Attention of one wave over entries [e0, e0 + ne) of request r, KV head h;
 // j_lane is the selected block of entry e0 + lane (loaded by the caller).
 // Leaves the running max (log2 domain) and the lane-group-reduced sum for

@@ -70,6 +70,44 @@ __device__ inline float elem_to_float<PULSE_F16>(uint16_t x) {
     return (float)h;
 }
 
+// ---- MFMA operands ---------------------------------------------------------
+
+template <int DT>
+struct Mfma;
+template <>
+struct Mfma<PULSE_BF16> {
+    typedef bf16x8 vec;
+    typedef __bf16 elem;
+    __device__ static inline f32x4 mac(vec a, vec b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    }
+    __device__ static inline void split(float p, __bf16& hi, __bf16& lo) {
+        hi = (__bf16)p;
+        lo = (__bf16)(p - (float)hi);
+    }
+};
+template <>
+struct Mfma<PULSE_F16> {
+    typedef f16x8 vec;
+    typedef _Float16 elem;
+    __device__ static inline f32x4 mac(vec a, vec b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+    }
+    __device__ static inline void split(float p, _Float16& hi, _Float16& lo) {
+        hi = (_Float16)p;
+        lo = (_Float16)(p - (float)hi);
+    }
+};
+
+template <int DT>
+__device__ inline typename Mfma<DT>::vec load_vec(const uint16_t* p) {
+    return __builtin_bit_cast(typename Mfma<DT>::vec, *reinterpret_cast<const u32x4*>(p));
+}
+template <int DT>
+__device__ inline typename Mfma<DT>::vec zero_vec() {
+    return __builtin_bit_cast(typename Mfma<DT>::vec, u32x4{0, 0, 0, 0});
+}
+
 // ---- workspace layout -----------------------------------------------------
 
 struct AttnPlan {
@@ -218,11 +256,15 @@ hipError_t launch_attention(const pulse_shape& s, const void* q, const void* poo
                             hipEvent_t done = nullptr);
 
 hipError_t launch_average_scores(const float* sc, int64_t total_blocks, int32_t H, float* avg, hipStream_t st);
-hipError_t launch_mam_selection(const int32_t* ctx_len, int32_t B, int32_t bs, int32_t max_blocks, int32_t n_sink,
-                                int32_t n_local, int32_t* sel_all, int32_t* cnt_all, int32_t* sel_mid,
-                                int32_t* cnt_mid, int32_t* status, hipStream_t st);
-hipError_t launch_mam_finalize(const float* lse_all, const float* lse_mid, int32_t B, int32_t Hkv, int32_t G,
-                               float* mam, hipStream_t st);
+// Middle Attention Mass (variants.hip): the split of the context pass and its launch.
+struct MamPlan {
+    int32_t entries_per_wave;  // blocks of one wave (at most 64)
+    int32_t n_wg;              // workgroups per (request, KV head)
+};
+MamPlan mam_plan(int32_t B, int32_t Hkv, int32_t max_blocks, int32_t bs);
+hipError_t launch_mam(const pulse_shape& s, const void* q, const void* pool, int32_t n_slots, const int32_t* table,
+                      int32_t max_blocks, const int32_t* ctx_len, int32_t B, int32_t n_sink, int32_t n_local,
+                      float sm_scale, float* mam, float4* part, int32_t* status, hipStream_t st);
 
 // Host-side argument check: return `code` from the calling entry point.
 #define PULSE_REQUIRE(cond, code)   \
