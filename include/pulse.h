@@ -228,8 +228,8 @@ PULSE_API pulse_status pulse_select_average(const pulse_shape* shape, const void
  * mean of MAM_q over its G query heads:
  *   mam[r][h] = (1/G) sum_g exp(lse_middle(r, hG+g) - lse_all(r, hG+g)),
  * with lse the natural log-sum-exp of the logits q.k * sm_scale.  Computed
- * with the sparse attention kernel over every block and over the middle
- * blocks (fp32; no middle blocks -> 0).
+ * as the ratio of the two sums of exp(logit), both taken in one pass over the
+ * keys (fp32; no middle blocks -> 0).
  *   slot_pool / block_table  as for pulse_sparse_decode_attn; every block of
  *            every request must be resident (block_table[r][j] valid for
  *            j < ceil(ctx_len[r] / block_size) <= max_blocks), else

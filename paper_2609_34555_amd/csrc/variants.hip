@@ -39,7 +39,9 @@ hipError_t launch_average_scores(const float* sc, int64_t total_blocks, int32_t 
 }
 
 constexpr int kMamWaves = 4;
-constexpr int64_t kMamTargetWaves = 4096;
+// Waves of a call: two per SIMD.  4 x 32K tokens took 58.0 / 59.1 / 58.1 us at 2048 / 4096 / 8192, one request
+// of 55K tokens with 4 KV heads 19.0 / 20.6 / 20.6 (more partials to merge).
+constexpr int64_t kMamTargetWaves = 2048;
 constexpr int kMamStep = 32;  // tokens per MFMA step
 
 // Softmax sums of one query column over part of the context.
@@ -192,12 +194,19 @@ __global__ __launch_bounds__(kMamWaves * kWave) void mam_kernel(
     }
 }
 
-// Merge of the workgroup partials: grid = (Hkv, B), one wave; lane = (query head, quarter of the partials).
-__global__ __launch_bounds__(kWave) void mam_merge_kernel(const float4* __restrict__ part, int32_t n_wg,
-                                                          const int32_t* __restrict__ ctx_len, int32_t bs,
-                                                          int32_t max_blocks, int32_t epw, int32_t G,
-                                                          float* __restrict__ mam) {
-    const int lane = threadIdx.x, g = lane & 15;
+// Merge of the workgroup partials: grid = (Hkv, B); thread = (query head, one of
+// kMamMergeThreads / 16 streams of partials), so a context split over hundreds of
+// workgroups is a few dependent merges per thread (with one wave per head, 217 partials
+// of a 55K-token request, 4 KV heads, took most of the call: 36 us, now 19).
+constexpr int kMamMergeThreads = 512;
+
+__global__ __launch_bounds__(kMamMergeThreads) void mam_merge_kernel(const float4* __restrict__ part, int32_t n_wg,
+                                                                     const int32_t* __restrict__ ctx_len, int32_t bs,
+                                                                     int32_t max_blocks, int32_t epw, int32_t G,
+                                                                     float* __restrict__ mam) {
+    constexpr int kStreams = kMamMergeThreads / kMaxGroup;
+    __shared__ float4 s_part[kMamMergeThreads / kWave][kMaxGroup];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane & 15;
     const int h = blockIdx.x, Hkv = gridDim.x, r = blockIdx.y;
     const int64_t ctx = ctx_len[r];
     int64_t n = ctx > 0 ? (ctx + bs - 1) / bs : 0;
@@ -208,14 +217,19 @@ __global__ __launch_bounds__(kWave) void mam_merge_kernel(const float4* __restri
     MamSum sum;
     if (g < G) {
 #pragma unroll 4
-        for (int i = lane >> 4; i < nw; i += 4) {
+        for (int i = tid >> 4; i < nw; i += kStreams) {
             const float4 v = p[(size_t)i * G + g];
             sum.merge(v.x, v.y, v.z);
         }
     }
     sum.merge_lanes(16);
     sum.merge_lanes(32);
-    const float mean = mean_mass(sum.mass(), G);
+    if (lane < kMaxGroup) s_part[wave][lane] = make_float4(sum.m, sum.all, sum.mid, 0.f);
+    __syncthreads();
+    if (wave > 0) return;
+    MamSum tot;
+    for (int w = 0; w < kMamMergeThreads / kWave; ++w) tot.merge(s_part[w][g].x, s_part[w][g].y, s_part[w][g].z);
+    const float mean = mean_mass(tot.mass(), G);
     if (lane == 0) mam[(size_t)r * Hkv + h] = mean;
 }
 
@@ -257,7 +271,7 @@ hipError_t launch_mam(const pulse_shape& s, const void* q, const void* pool, int
 #undef PULSE_MAM
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.n_wg == 1) return e;
-    hipLaunchKernelGGL(mam_merge_kernel, dim3((unsigned)Hkv, (unsigned)B), dim3(kWave), 0, st, (const float4*)part,
+    hipLaunchKernelGGL(mam_merge_kernel, dim3((unsigned)Hkv, (unsigned)B), dim3(kMamMergeThreads), 0, st, (const float4*)part,
                        p.n_wg, ctx_len, s.block_size, max_blocks, p.entries_per_wave, G, mam);
     return hipGetLastError();
 }
