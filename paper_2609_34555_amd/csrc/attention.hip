@@ -198,7 +198,8 @@ __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
     const int32_t* __restrict__ table, int32_t max_blocks, const int32_t* __restrict__ sel_idx,
     const int32_t* __restrict__ sel_cnt, int32_t k_max, const int32_t* __restrict__ ctx_len, int32_t Hq,
     int32_t Hkv, int32_t G, int32_t eps, int32_t n_wg, float scale_log2, float* __restrict__ ws_o,
-    float2* __restrict__ ws_ml, float* __restrict__ out, float* __restrict__ lse, int32_t* status) {
+    float2* __restrict__ ws_ml, float* __restrict__ out, float* __restrict__ lse, __bf16* __restrict__ x,
+    int32_t* status) {
     extern __shared__ float smem[];
     constexpr int kThreads = W * kWave;
     float* s_o = smem;                                                           // [W][G][128]
@@ -208,6 +209,7 @@ __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
     const int wg = blockIdx.x, h = blockIdx.y, r = blockIdx.z;
     float* out_rh = out + ((size_t)r * Hq + (size_t)h * G) * kHeadDim;
     float* lse_rh = lse ? lse + (size_t)r * Hq + (size_t)h * G : nullptr;
+    __bf16* x_rh = x ? x + ((size_t)r * Hq + (size_t)h * G) * kHeadDim : nullptr;
 
     // this wave's selected blocks (one per lane) are loaded with the count they
     // depend on, not after it: one memory round trip fewer before the first K load
@@ -223,7 +225,10 @@ __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
     const int nwg = (ns + W - 1) / W;  // workgroups with work
     if (wg >= nwg) {
         if (cnt == 0 && wg == 0) {  // empty selection: out = 0, lse = -inf
-            for (int i = tid; i < G * kHeadDim; i += kThreads) out_rh[i] = 0.f;
+            for (int i = tid; i < G * kHeadDim; i += kThreads) {
+                out_rh[i] = 0.f;
+                if (x_rh) x_rh[i] = (__bf16)0.f;
+            }
             if (lse_rh && tid < G) lse_rh[tid] = -INFINITY;
         }
         return;
@@ -263,7 +268,9 @@ __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
             }
         }
         if (nwg == 1) {
-            out_rh[idx] = Mx == -INFINITY ? 0.f : a / L;
+            const float o = Mx == -INFINITY ? 0.f : a / L;
+            out_rh[idx] = o;
+            if (x_rh) x_rh[idx] = (__bf16)o;
             if (lse_rh && c == 0) lse_rh[g] = Mx == -INFINITY ? -INFINITY : (Mx + log2f(L)) * 0.69314718055994531f;
         } else {
             ws_o[unit * G * kHeadDim + idx] = a;
@@ -280,7 +287,7 @@ __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
 __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
     const float* __restrict__ ws_o, const float2* __restrict__ ws_ml, const int32_t* __restrict__ sel_cnt,
     int32_t k_max, int32_t Hq, int32_t Hkv, int32_t G, int32_t eps, int32_t n_wg, int32_t waves,
-    float* __restrict__ out, float* __restrict__ lse) {
+    float* __restrict__ out, float* __restrict__ lse, __bf16* __restrict__ x) {
     const int c = threadIdx.x, g = blockIdx.x, h = blockIdx.y, r = blockIdx.z;
     const size_t u0 = ((size_t)r * Hkv + h) * n_wg;
     const float2* ml = ws_ml + u0 * G + g;                  // stride G
@@ -331,8 +338,10 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
         }
         m_run = cm;
     }
-    float* out_rg = out + ((size_t)r * Hq + (size_t)h * G + g) * kHeadDim;
-    out_rg[c] = m_run == -INFINITY ? 0.f : a / L;
+    const size_t at = ((size_t)r * Hq + (size_t)h * G + g) * kHeadDim + c;
+    const float o = m_run == -INFINITY ? 0.f : a / L;
+    out[at] = o;
+    if (x) x[at] = (__bf16)o;
     if (lse && c == 0)
         lse[(size_t)r * Hq + (size_t)h * G + g] =
             m_run == -INFINITY ? -INFINITY : (m_run + log2f(L)) * 0.69314718055994531f;
@@ -364,17 +373,17 @@ static void launch_attn_t(dim3 grid, size_t lds, hipStream_t st, hipEvent_t done
                           int32_t n_slots, const int32_t* table, int32_t max_blocks, const int32_t* sel_idx,
                           const int32_t* sel_cnt, int32_t k_max, const int32_t* ctx_len, int32_t Hq, int32_t Hkv,
                           int32_t G, int32_t eps, int32_t n_wg, float scale_log2, float* ws_o, float2* ws_ml,
-                          float* out, float* lse, int32_t* status) {
+                          float* out, float* lse, __bf16* x, int32_t* status) {
     launch_timed(attn_splitk_kernel<DT, BS, W>, grid, dim3(W * kWave), (uint32_t)lds, st, nullptr, done,
                  (const uint16_t*)q, (const uint16_t*)pool, n_slots, table, max_blocks, sel_idx, sel_cnt, k_max,
-                 ctx_len, Hq, Hkv, G, eps, n_wg, scale_log2, ws_o, ws_ml, out, lse, status);
+                 ctx_len, Hq, Hkv, G, eps, n_wg, scale_log2, ws_o, ws_ml, out, lse, x, status);
 }
 
 hipError_t launch_attention(const pulse_shape& s, const void* q, const void* pool, int32_t n_slots,
                             const int32_t* table, int32_t max_blocks, const int32_t* sel_idx, const int32_t* sel_cnt,
                             int32_t k_max, const int32_t* ctx_len, int32_t B, float sm_scale, float* out, float* lse,
                             float* ws_o, float2* ws_ml, int32_t* status, hipStream_t st, hipEvent_t split_done,
-                            hipEvent_t done) {
+                            hipEvent_t done, __bf16* x) {
     if (B == 0) return hipSuccess;
     const int32_t Hkv = s.num_kv_heads, Hq = s.num_q_heads, G = Hq / Hkv;
     const AttnPlan p = attn_plan(B, Hkv, k_max, s.block_size);
@@ -388,7 +397,7 @@ hipError_t launch_attention(const pulse_shape& s, const void* q, const void* poo
 #define PULSE_ATTN(DT, BS, W)                                                                                        \
     launch_attn_t<DT, BS, W>(grid, lds, st, splitk_stop, q, pool, n_slots, table, max_blocks, sel_idx, sel_cnt,     \
                              k_max, ctx_len,                                                                        \
-                             Hq, Hkv, G, p.entries_per_split, n_wg, scale_log2, ws_o, ws_ml, out, lse, status)
+                             Hq, Hkv, G, p.entries_per_split, n_wg, scale_log2, ws_o, ws_ml, out, lse, x, status)
 #define PULSE_ATTN_W(DT, BS) \
     if (W == 8) PULSE_ATTN(DT, BS, 8); else PULSE_ATTN(DT, BS, 4)
     if (s.dtype == PULSE_BF16) {
@@ -407,7 +416,7 @@ hipError_t launch_attention(const pulse_shape& s, const void* q, const void* poo
     if (n_wg <= 1) return (done && split_done) ? hipEventRecord(done, st) : hipSuccess;
     launch_timed(attn_combine_kernel, dim3((unsigned)G, (unsigned)Hkv, (unsigned)B), dim3(kCombineThreads), 0u, st,
                  nullptr, done, (const float*)ws_o, (const float2*)ws_ml, sel_cnt, k_max, Hq, Hkv, G,
-                 p.entries_per_split, n_wg, W, out, lse);
+                 p.entries_per_split, n_wg, W, out, lse, x);
     return hipGetLastError();
 }
 

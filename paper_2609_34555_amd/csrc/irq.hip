@@ -33,7 +33,7 @@
 //
 // A normal-batch layer is decode attention over its resident KV (every
 // block selected; the attention kernel of this library) followed by a SwiGLU
-// FFN on the attention output: x = bf16(out), [g|u] = x W_gu^T, h = silu(g) *
+// FFN on the attention output: x = bf16(out) (written by the attention), [g|u] = x W_gu^T, h = silu(g) *
 // u, y = h W_down^T (bf16, fp32 accumulation; the two GEMMs are the MFMA
 // kernel below).  Projections and norms are left out.
 #include <chrono>
@@ -48,98 +48,151 @@ __global__ void irq_signal_kernel(int64_t* flag, int64_t value) {
         __hip_atomic_store(flag, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-__global__ __launch_bounds__(256) void to_bf16_kernel(const float* __restrict__ in, __bf16* __restrict__ out,
-                                                      int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        out[i] = (__bf16)in[i];
-}
-
-// h[b][i] = silu(gu[b][i]) * gu[b][F + i], in fp32, rounded to bf16.
-__global__ __launch_bounds__(256) void swiglu_kernel(const __bf16* __restrict__ gu, __bf16* __restrict__ h, int32_t B,
-                                                     int32_t F) {
-    const int64_t n = (int64_t)B * F;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t b = i / F, c = i % F;
-        const float g = (float)gu[b * 2 * F + c];
-        const float u = (float)gu[b * 2 * F + F + c];
-        h[i] = (__bf16)(g / (1.f + expf(-g)) * u);
-    }
-}
-
 // ---- the FFN's GEMMs ------------------------------------------------------
 // C[M][N] = A[M][K] . Wt[N][K]^T with bf16 inputs, fp32 accumulation and a bf16
 // (round-to-nearest-even) result: the shape of a decode batch's projections,
-// M (requests) small and N, K model widths, so the weight rows dominate the
-// traffic.  A workgroup of kGemmWaves waves owns 16 * NT output columns and
-// 16 * MT rows.  Its waves split K: wave w takes kGemmUnroll consecutive
-// 32-element steps at a time (every weight row is read in 256-byte runs), all
-// their loads in flight before the products.  Per step a lane loads 16
-// contiguous bytes of one weight row per column tile (B operand: column =
-// lane % 16, k = 8 * (lane / 16) ...) and of one activation row per row tile
-// (A operand), and v_mfma_f32_16x16x32_bf16 accumulates each 16 x 16 tile
-// (lane holds rows 4 * (lane / 16) + v, column lane % 16).  Weights are loaded
-// non-temporally: they are read once, and the activations (read by every
-// workgroup) then stay in L2.  The waves' partial tiles are summed in LDS.
+// M (requests) small and N, K model widths, so the weights, read once, bound
+// both products.  A workgroup of WV waves owns CT column tiles of 16 (PAIR: CT
+// gate tiles and the CT up tiles they are multiplied with) and 16 * MT rows; its
+// waves split K, each taking groups of U 32-element steps, and their partial
+// tiles are summed in LDS.  Products are v_mfma_f32_16x16x32_bf16 (B operand:
+// column = lane % 16, k = 8 * (lane / 16) ...; A operand likewise by rows; lane
+// holds rows 4 * (lane / 16) + v, column lane % 16).
+//
+// In that operand layout neighbouring lanes hold different rows, and a load in
+// it costs the cache one lookup per lane: about one 16-byte piece per clock and
+// CU, which, not HBM, bound these products (32 x 14336 x 4096: activations
+// alone 26 us, weights alone 23, both 45, whatever was in flight).  So each wave loads
+// its rows with neighbouring lanes on neighbouring pieces, puts them into its
+// own part of LDS and reads the operands there; piece p of row r lies at
+// position p ^ r, which spreads the 16 rows of an operand over all banks.
+// The next group is loaded before this one's products.  Workgroups start at
+// different groups of K (rows are a multiple of 4 KiB apart, so in step they
+// would all ask the same L2 channels; 1 us).  Weights are loaded non-temporally:
+// the activations, read by every workgroup, then stay in L2.
 // K must be a multiple of 8 and rows 16-byte aligned.
-constexpr int kGemmWaves = 8;
-
-template <int MT, int NT, int U>
-__global__ __launch_bounds__(kGemmWaves * kWave) void ffn_gemm_kernel(const __bf16* __restrict__ A,
-                                                                      const __bf16* __restrict__ Wt,
-                                                                      __bf16* __restrict__ C, int32_t M, int32_t N,
-                                                                      int32_t K) {
-    __shared__ float red[kGemmWaves][NT][MT][4][kWave];
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+template <int MT, int CT, int U, int WV, bool PAIR>
+__global__ __launch_bounds__(WV * kWave) void ffn_gemm_kernel(const __bf16* __restrict__ A,
+                                                              const __bf16* __restrict__ Wt,
+                                                              __bf16* __restrict__ C, __bf16* __restrict__ H,
+                                                              int32_t M, int32_t N, int32_t K) {
+    constexpr int NT = PAIR ? 2 * CT : CT;  // column tiles: CT of the output (PAIR: CT gate tiles, then CT up tiles)
+    constexpr int PP = 4 * U;                   // 16-byte pieces of a row in one group of steps
+    constexpr int RT = MT + NT;                 // row tiles staged per group: activations, then weights
+    constexpr int NA = 16 * MT * PP / kWave, NB = 16 * NT * PP / kWave;  // pieces a lane stages per group
+    constexpr int kStage = WV * 16 * RT * PP * 16, kRed = WV * NT * MT * 4 * kWave * 4;
+    __shared__ __align__(16) uint8_t smem[kStage > kRed ? kStage : kRed];
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int col = lane & 15, grp = lane >> 4;
-    const int n0 = blockIdx.x * 16 * NT, m0 = blockIdx.y * 16 * MT;
+    const int n0 = blockIdx.x * 16 * CT, m0 = blockIdx.y * 16 * MT;
+    // columns past N and rows past M repeat the first one; their products are dropped
     const __bf16* wrow[NT];
-    bool n_ok[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-        const int n = n0 + 16 * nt + col;
-        n_ok[nt] = n < N;
-        wrow[nt] = Wt + (size_t)(n_ok[nt] ? n : 0) * K + grp * 8;
+        const int n = n0 + nt % CT * 16 + col;
+        wrow[nt] = Wt + ((size_t)(nt / CT) * N + (n < N ? n : 0)) * K + grp * 8;
     }
     const __bf16* arow[MT];
-    bool m_ok[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         const int m = m0 + 16 * mt + col;
-        m_ok[mt] = m < M;
-        arow[mt] = A + (size_t)(m_ok[mt] ? m : 0) * K + grp * 8;
+        arow[mt] = A + (size_t)(m < M ? m : 0) * K + grp * 8;
     }
-    const u32x4 zero = {0, 0, 0, 0};
     f32x4 acc[NT][MT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int steps = (K + 31) / 32;
-    for (int sb = wave * U; sb < steps; sb += kGemmWaves * U) {
-        u32x4 b[U][NT], a[U][MT];
+    u32x4* stage = reinterpret_cast<u32x4*>(smem) + wave * 16 * RT * PP;
+    const __bf16* astage[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int row = (i * kWave + lane) / PP, p = lane % PP;
+        astage[i] = A + (size_t)(m0 + row < M ? m0 + row : 0) * K + (p ^ (row % PP)) * 8;
+    }
+    const __bf16* wstage[NB];
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int row = (i * kWave + lane) / PP, p = lane % PP;
+        const int n = n0 + row % (16 * CT);
+        wstage[i] = Wt + ((size_t)(row / (16 * CT)) * N + (n < N ? n : 0)) * K + (p ^ (row % PP)) * 8;
+    }
+    auto load = [&](int j, u32x4 (&a)[NA], u32x4 (&b)[NB]) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) a[i] = *reinterpret_cast<const u32x4*>(astage[i] + j * U * 32);
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+            b[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(wstage[i] + j * U * 32));
+        __builtin_amdgcn_sched_barrier(0);  // ahead of the products that follow
+    };
+    auto products = [&](const u32x4 (&a)[NA], const u32x4 (&b)[NB]) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) stage[i * kWave + lane] = a[i];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) stage[(NA + i) * kWave + lane] = b[i];
+        auto frag = [&](int tile, int u) {
+            return stage[(16 * tile + col) * PP + ((u * 4 + grp) ^ (col % PP))];
+        };
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int k = (sb + u) * 32;  // this lane's 8 elements start at k + 8 * grp
-            const bool k_ok = k + grp * 8 < K;
+            u32x4 bv[NT];
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-                b[u][nt] = (k_ok && n_ok[nt])
-                               ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(wrow[nt] + k))
-                               : zero;
+            for (int nt = 0; nt < NT; ++nt) bv[nt] = frag(MT + nt, u);
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                a[u][mt] = (k_ok && m_ok[mt]) ? *reinterpret_cast<const u32x4*>(arow[mt] + k) : zero;
-        }
+            for (int mt = 0; mt < MT; ++mt) {
+                const u32x4 av = frag(mt, u);
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[u][mt]),
-                                                                          __builtin_bit_cast(bf16x8, b[u][nt]),
+                for (int nt = 0; nt < NT; ++nt)
+                    acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av),
+                                                                          __builtin_bit_cast(bf16x8, bv[nt]),
                                                                           acc[nt][mt], 0, 0, 0);
+            }
+        }
+    };
+    // Groups that lie within K, every WV-th to each wave, loaded without a test (a test per load
+    // makes the compiler wait for all loads in flight at every product).
+    u32x4 a0[NA], a1[NA], b0[NB], b1[NB];
+    const int groups = K / (32 * U);
+    if (wave < groups) {
+        const int mine = (groups - wave + WV - 1) / WV;
+        const int rot = (int)(blockIdx.x / 8) % mine;
+        auto at = [&](int i) { const int ii = i + rot; return wave + (ii < mine ? ii : ii - mine) * WV; };
+        load(at(0), a0, b0);
+        int i = 0;
+        for (; i + 2 < mine; i += 2) {
+            load(at(i + 1), a1, b1);
+            products(a0, b0);
+            load(at(i + 2), a0, b0);
+            products(a1, b1);
+        }
+        if (i + 1 < mine) {
+            load(at(i + 1), a1, b1);
+            products(a0, b0);
+            products(a1, b1);
+        } else {
+            products(a0, b0);
+        }
     }
+    if (wave == groups % WV) {  // the rest of K: whole steps and a last one of 8, 16 or 24 elements
+        for (int k = groups * 32 * U; k < K; k += 32) {
+            const bool ok = k + grp * 8 < K;
+            const u32x4 zero = {0, 0, 0, 0};
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const u32x4 bv = ok ? *reinterpret_cast<const u32x4*>(wrow[nt] + k) : zero;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    const u32x4 av = ok ? *reinterpret_cast<const u32x4*>(arow[mt] + k) : zero;
+                    acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av),
+                                                                          __builtin_bit_cast(bf16x8, bv),
+                                                                          acc[nt][mt], 0, 0, 0);
+                }
+            }
+        }
+    }
+    __syncthreads();  // the staged rows are read
+    float(*red)[NT][MT][4][kWave] = reinterpret_cast<float(*)[NT][MT][4][kWave]>(smem);
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -147,169 +200,63 @@ __global__ __launch_bounds__(kGemmWaves * kWave) void ffn_gemm_kernel(const __bf
 #pragma unroll
             for (int v = 0; v < 4; ++v) red[wave][nt][mt][v][lane] = acc[nt][mt][v];
     __syncthreads();
-    for (int o = tid; o < 16 * MT * 16 * NT; o += kGemmWaves * kWave) {
-        const int ml = o / (16 * NT), nl = o % (16 * NT);  // row of the workgroup's rows, column of its columns
-        const int mt = ml / 16, i = ml % 16, nt = nl / 16;
+    for (int o = tid; o < 16 * MT * 16 * CT; o += WV * kWave) {
+        const int ml = o / (16 * CT), nl = o % (16 * CT);  // row of the workgroup's rows, column of its columns
+        const int mt = ml / 16, i = ml % 16;
         const int v = i % 4, src = (i / 4) * 16 + nl % 16;
-        float sum = 0.f;
+        float sum[NT / CT];
 #pragma unroll
-        for (int w = 0; w < kGemmWaves; ++w) sum += red[w][nt][mt][v][src];
-        const int m = m0 + ml, n = n0 + nl;
-        if (m < M && n < N) C[(size_t)m * N + n] = (__bf16)sum;
+        for (int p = 0; p < NT / CT; ++p) {
+            sum[p] = 0.f;
+#pragma unroll
+            for (int w = 0; w < WV; ++w) sum[p] += red[w][p * CT + nl / 16][mt][v][src];
+        }
+        const int m = m0 + ml, nn = n0 + nl;
+        if (m >= M || nn >= N) continue;
+        if constexpr (PAIR) {
+            const __bf16 gb = (__bf16)sum[0], ub = (__bf16)sum[1];
+            C[(size_t)m * 2 * N + nn] = gb;
+            C[(size_t)m * 2 * N + N + nn] = ub;
+            const float g = (float)gb, u = (float)ub;
+            H[(size_t)m * N + nn] = (__bf16)(g / (1.f + expf(-g)) * u);
+        } else {
+            C[(size_t)m * N + nn] = (__bf16)sum[0];
+        }
     }
 }
 
-// The same product for wide outputs (many column tiles), with the activations shared
-// through LDS: a workgroup's 8 waves are CG = 8 / KG column groups of 16 * NT
-// columns times KG K-groups.  K advances in chunks of KC = KG * U * 32 elements;
-// each chunk of the workgroup's 16 * MT activation rows is staged once in LDS
-// (double-buffered, rows padded by 16 bytes against bank conflicts) and read by
-// all column groups, while every wave prefetches its weights of the next chunk.
-// The K-groups' partial tiles are summed in LDS at the end.
-template <int MT, int NT, int KG, int U>
-__global__ __launch_bounds__(kGemmWaves * kWave) void ffn_gemm_lds_kernel(const __bf16* __restrict__ A,
-                                                                          const __bf16* __restrict__ Wt,
-                                                                          __bf16* __restrict__ C, int32_t M,
-                                                                          int32_t N, int32_t K) {
-    constexpr int CG = kGemmWaves / KG;
-    constexpr int KC = KG * U * 32;    // K elements per chunk
-    constexpr int ROWS = 16 * MT;
-    constexpr int PITCH = KC + 8;      // elements per staged row
-    constexpr int PIECES = ROWS * KC / 8;  // 16-byte pieces of a chunk
-    constexpr int kThreads = kGemmWaves * kWave;
-    constexpr int kStageBytes = 2 * ROWS * PITCH * 2;
-    constexpr int kRedBytes = KG * CG * NT * MT * 4 * kWave * 4;
-    static_assert(PIECES % kThreads == 0, "a chunk is an exact number of pieces per thread");
-    __shared__ __align__(16) uint8_t smem[kStageBytes > kRedBytes ? kStageBytes : kRedBytes];
-    uint16_t(*sa)[ROWS][PITCH] = reinterpret_cast<uint16_t(*)[ROWS][PITCH]>(smem);
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    const int col = lane & 15, grp = lane >> 4;
-    const int cg = wave % CG, kg = wave / CG;
-    const int n0 = blockIdx.x * 16 * NT * CG + cg * 16 * NT, m0 = blockIdx.y * ROWS;
-    const __bf16* wrow[NT];
-    bool n_ok[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        const int n = n0 + 16 * nt + col;
-        n_ok[nt] = n < N;
-        wrow[nt] = Wt + (size_t)(n_ok[nt] ? n : 0) * K + grp * 8;
-    }
-    const u32x4 zero = {0, 0, 0, 0};
-    // this thread's pieces of an activation chunk: row, element offset
-    auto stage_load = [&](int k0, u32x4 (&ra)[PIECES / kThreads]) {
-#pragma unroll
-        for (int i = 0; i < PIECES / kThreads; ++i) {
-            const int pc = tid + i * kThreads;
-            const int row = pc / (KC / 8), kk = (pc % (KC / 8)) * 8;
-            const int m = m0 + row, k = k0 + kk;
-            ra[i] = (m < M && k < K) ? *reinterpret_cast<const u32x4*>(A + (size_t)m * K + k) : zero;
-        }
-    };
-    auto stage_store = [&](int buf, const u32x4 (&ra)[PIECES / kThreads]) {
-#pragma unroll
-        for (int i = 0; i < PIECES / kThreads; ++i) {
-            const int pc = tid + i * kThreads;
-            const int row = pc / (KC / 8), kk = (pc % (KC / 8)) * 8;
-            *reinterpret_cast<u32x4*>(&sa[buf][row][kk]) = ra[i];
-        }
-    };
-    auto load_w = [&](int k0, u32x4 (&b)[U][NT]) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int k = k0 + (kg * U + u) * 32;  // this lane's 8 elements start at k + 8 * grp
-            const bool k_ok = k + grp * 8 < K;
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-                b[u][nt] = (k_ok && n_ok[nt])
-                               ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(wrow[nt] + k))
-                               : zero;
-        }
-    };
-    f32x4 acc[NT][MT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int n_chunks = (K + KC - 1) / KC;
-    u32x4 ra[PIECES / kThreads], b[U][NT], bn[U][NT];
-    stage_load(0, ra);
-    load_w(0, b);
-    stage_store(0, ra);
-    __syncthreads();
-    for (int it = 0; it < n_chunks; ++it) {
-        const bool more = it + 1 < n_chunks;
-        if (more) {  // next chunk's weights and activations in flight during this chunk's products
-            load_w((it + 1) * KC, bn);
-            stage_load((it + 1) * KC, ra);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const u32x4 af = *reinterpret_cast<const u32x4*>(&sa[it & 1][16 * mt + col][(kg * U + u) * 32 + grp * 8]);
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    acc[nt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, af),
-                                                                          __builtin_bit_cast(bf16x8, b[u][nt]),
-                                                                          acc[nt][mt], 0, 0, 0);
-            }
-        if (more) stage_store((it + 1) & 1, ra);
-        __syncthreads();
-        if (more) {
-#pragma unroll
-            for (int u = 0; u < U; ++u)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) b[u][nt] = bn[u][nt];
-        }
-    }
-    // the staging buffers are free now (the loop ended with a barrier): K-group partials
-    float(*red)[CG][NT][MT][4][kWave] = reinterpret_cast<float(*)[CG][NT][MT][4][kWave]>(smem);
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) red[kg][cg][nt][mt][v][lane] = acc[nt][mt][v];
-    __syncthreads();
-    constexpr int COLS = 16 * NT * CG;
-    const int nb = blockIdx.x * COLS;
-    for (int o = tid; o < ROWS * COLS; o += kThreads) {
-        const int ml = o / COLS, nl = o % COLS;  // row of the workgroup's rows, column of its columns
-        const int g = nl / (16 * NT), nt = (nl / 16) % NT, mt = ml / 16, i = ml % 16;
-        const int v = i % 4, src = (i / 4) * 16 + nl % 16;
-        float sum = 0.f;
-#pragma unroll
-        for (int w = 0; w < KG; ++w) sum += red[w][g][nt][mt][v][src];
-        const int m = m0 + ml, n = nb + nl;
-        if (m < M && n < N) C[(size_t)m * N + n] = (__bf16)sum;
-    }
-}
-
-// Wide outputs (N >= 16384: at least 256 workgroups of 64 columns) with at most 32 rows use
-// the LDS kernel with 4 column groups of 16 columns x 2 K-groups (measured on 32 x 4096 x 28672:
-// 58.9 us, against 64.0 with 128 columns per workgroup and 60.1 with 8 column groups and one
-// K-group); the others the direct kernel with 16 columns per workgroup (enough workgroups for
-// narrow outputs: 48 us on 32 x 14336 x 4096, 66 with 32 columns).
-static hipError_t launch_ffn_gemm(const void* A, const void* Wt, void* C, int32_t M, int32_t N, int32_t K,
+// PAIR: gu [M][2N] = A . Wt^T for the N gate and N up rows of Wt, H [M][N] = silu(g) * u of the rounded values.
+//
+// Tiles, at 32 rows (M <= 32; larger M reads the weights once per 64 rows):
+//   gate and up, 4096 -> 2 x 14336 (235 MB): two tiles of each per workgroup of 4 waves, so that the activations
+//   are read half as often, 40.7 us (5.8 TB/s); one tile, 8 waves 47.2; two tiles, 8 waves 46.1; two tiles in steps
+//   of 1 59.3.  Below 512 column tiles two per workgroup would leave CUs idle.
+//   down, 14336 -> 4096 (117 MB): one tile, 8 waves, steps of 4: 27.8 us (4.2 TB/s); two tiles (half the CUs) 34.7;
+//   steps of 2 29.9, 16 waves in steps of 2 30.8.
+// The form before, operands loaded in their layout: 61.4 us + 4.8 of a SwiGLU kernel, and 49.7.
+template <bool PAIR>
+static hipError_t launch_ffn_gemm(const void* A, const void* Wt, void* C, void* H, int32_t M, int32_t N, int32_t K,
                                   hipStream_t st) {
-    const __bf16* a = (const __bf16*)A;
-    const __bf16* w = (const __bf16*)Wt;
-    __bf16* c = (__bf16*)C;
-    const dim3 block(kGemmWaves * kWave);
-    if (N >= 16384 && M <= 32) {
-        constexpr int CG = 4, NT = 1;
-        const dim3 grid((unsigned)((N + 16 * NT * CG - 1) / (16 * NT * CG)), (unsigned)((M + 31) / 32));
-        hipLaunchKernelGGL((ffn_gemm_lds_kernel<2, NT, kGemmWaves / CG, 4>), grid, block, 0, st, a, w, c, M, N, K);
-    } else if (M <= 16) {
-        hipLaunchKernelGGL((ffn_gemm_kernel<1, 1, 4>), dim3((unsigned)((N + 15) / 16), (unsigned)((M + 15) / 16)),
-                           block, 0, st, a, w, c, M, N, K);
-    } else if (M <= 32) {
-        hipLaunchKernelGGL((ffn_gemm_kernel<2, 1, 4>), dim3((unsigned)((N + 15) / 16), (unsigned)((M + 31) / 32)),
-                           block, 0, st, a, w, c, M, N, K);
+    const unsigned nx = (unsigned)((N + 15) / 16);
+#define PULSE_GEMM(MT, CT, U, WV)                                                                                    \
+    hipLaunchKernelGGL((ffn_gemm_kernel<MT, CT, U, WV, PAIR>),                                                       \
+                       dim3((nx + CT - 1) / CT, (unsigned)((M + 16 * MT - 1) / (16 * MT))), dim3(WV * kWave), 0, st, \
+                       (const __bf16*)A, (const __bf16*)Wt, (__bf16*)C, (__bf16*)H, M, N, K)
+    if (M > 32) {
+        PULSE_GEMM(4, 1, 2, 8);
+    } else if constexpr (PAIR) {
+        if (nx >= 512) {
+            if (M <= 16) PULSE_GEMM(1, 2, 2, 4);
+            else PULSE_GEMM(2, 2, 2, 4);
+        } else {
+            if (M <= 16) PULSE_GEMM(1, 1, 2, 8);
+            else PULSE_GEMM(2, 1, 2, 8);
+        }
     } else {
-        hipLaunchKernelGGL((ffn_gemm_kernel<4, 1, 4>), dim3((unsigned)((N + 15) / 16), (unsigned)((M + 63) / 64)),
-                           block, 0, st, a, w, c, M, N, K);
+        if (M <= 16) PULSE_GEMM(1, 1, 4, 8);
+        else PULSE_GEMM(2, 1, 4, 8);
     }
+#undef PULSE_GEMM
     return hipGetLastError();
 }
 
@@ -317,11 +264,6 @@ static hipError_t launch_ffn_gemm(const void* A, const void* Wt, void* C, int32_
 // holds and the other XCDs keep serving HBM (from all XCDs, the concurrent layers
 // would barely progress until the recall ends).
 constexpr int32_t kIrqRecallXcds = 1;
-
-static unsigned grid_for(int64_t n) {
-    int64_t g = (n + 255) / 256;
-    return (unsigned)(g < 1 ? 1 : (g > 4096 ? 4096 : g));
-}
 
 }  // namespace pulse
 
@@ -374,20 +316,14 @@ static pulse_status normal_layer(pulse_irq* irq, const pulse_normal_layer& n, hi
     const WsLayout w = ws_layout(n.shape, n.B, n.k_max, 0);
     if (launch_attention(n.shape, n.q, n.slot_pool, n.n_slots, n.block_table, n.max_blocks, n.sel_idx, n.sel_cnt,
                          n.k_max, n.ctx_len, n.B, n.sm_scale, n.out, n.lse, ws_at<float>(n.ws, w.attn_o),
-                         ws_at<float2>(n.ws, w.attn_ml), n.dev_status, hs) != hipSuccess)
+                         ws_at<float2>(n.ws, w.attn_ml), n.dev_status, hs, nullptr, nullptr, (__bf16*)n.x) != hipSuccess)
         return PULSE_ERR_HIP;
     if (hipEventRecord(ev_attn, hs) != hipSuccess) return PULSE_ERR_HIP;
     const int32_t D = n.shape.num_q_heads * n.shape.head_dim, F = n.d_ff, B = n.B;
-    const int64_t nx = (int64_t)B * D;
-    hipLaunchKernelGGL(to_bf16_kernel, dim3(grid_for(nx)), dim3(256), 0, hs, n.out, (__bf16*)n.x, nx);
-    if (hipGetLastError() != hipSuccess) return PULSE_ERR_HIP;
-    // gu [B][2F] = x [B][D] . W_gu^T
-    if (launch_ffn_gemm(n.x, n.w_gate_up, n.gu, B, 2 * F, D, hs) != hipSuccess) return PULSE_ERR_HIP;
-    hipLaunchKernelGGL(swiglu_kernel, dim3(grid_for((int64_t)B * F)), dim3(256), 0, hs, (const __bf16*)n.gu,
-                       (__bf16*)n.h, B, F);
-    if (hipGetLastError() != hipSuccess) return PULSE_ERR_HIP;
+    // gu [B][2F] = x [B][D] . W_gu^T, h [B][F] = silu(g) * u
+    if (launch_ffn_gemm<true>(n.x, n.w_gate_up, n.gu, n.h, B, F, D, hs) != hipSuccess) return PULSE_ERR_HIP;
     // y [B][D] = h [B][F] . W_down^T
-    if (launch_ffn_gemm(n.h, n.w_down, n.y, B, D, F, hs) != hipSuccess) return PULSE_ERR_HIP;
+    if (launch_ffn_gemm<false>(n.h, n.w_down, n.y, nullptr, B, D, F, hs) != hipSuccess) return PULSE_ERR_HIP;
     if (hipEventRecord(ev_end, hs) != hipSuccess) return PULSE_ERR_HIP;
     return PULSE_OK;
 }

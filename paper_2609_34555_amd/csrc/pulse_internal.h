@@ -248,12 +248,13 @@ hipError_t launch_recall_copy(const void* host_kv, const int64_t* blk_off, int32
                               pulse_recall_stats* stats, int32_t* status, int32_t copy_xcds, hipStream_t st,
                               hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 
+// x (optional): [B][Hq][d], receives the output rounded to bf16 as well.
 hipError_t launch_attention(const pulse_shape& s, const void* q, const void* pool, int32_t n_slots,
                             const int32_t* table, int32_t max_blocks, const int32_t* sel_idx,
                             const int32_t* sel_cnt, int32_t k_max, const int32_t* ctx_len, int32_t B,
                             float sm_scale, float* out, float* lse, float* ws_o, float2* ws_ml,
                             int32_t* status, hipStream_t st, hipEvent_t split_done = nullptr,
-                            hipEvent_t done = nullptr);
+                            hipEvent_t done = nullptr, __bf16* x = nullptr);
 
 hipError_t launch_average_scores(const float* sc, int64_t total_blocks, int32_t H, float* avg, hipStream_t st);
 // Middle Attention Mass (variants.hip): the split of the context pass and its launch.

@@ -69,3 +69,45 @@ def test_mam_edges(ctx, hq, hkv, bs, dt, ns, nl):
     err = (out.double().cpu() - want).abs().max().item()
     say(f"  max err {err:.1e}")
     assert err < 1e-5
+
+
+# Rows of the FFN products per tile count (16, 32, 64 and beyond), hidden sizes below one group of
+# K steps, with a last step of 8 elements, and on either side of the two-tile rule (512 column tiles).
+FFN_CASES = [(1, 8, 2, 1, 100), (16, 24, 4, 2, 33), (17, 136, 8, 8, 16), (32, 1000, 4, 4, 300), (33, 512, 6, 3, 20),
+             (70, 264, 2, 2, 5), (5, 8184, 2, 1, 40), (31, 8192 + 8, 4, 1, 64)]
+
+
+@pytest.mark.parametrize("B,F,hq,hkv,ctx", FFN_CASES)
+def test_normal_layer_edges(B, F, hq, hkv, ctx):
+    from paper_2609_34555_amd.harness import NormalBatch
+    from paper_2609_34555_amd import workloads as W
+    from parity import build
+
+    say(f"\n[gpu] normal layer B={B} F={F} hq={hq} hkv={hkv} ctx={ctx}")
+    spec, seed = W.custom("light", [200], Hq=4, Hkv=2, bs=16, k_mid=2)
+    w, st = build(spec, seed)
+    st.reset()
+    normal = NormalBatch(B=B, ctx=ctx, n_layers=1, Hq=hq, Hkv=hkv, d_ff=F, seed=B + F)
+    cmp_, io = torch.cuda.Stream(), torch.cuda.Stream()
+    sched = P.IrqScheduler(cmp_, io)
+    torch.cuda.synchronize()
+    stats, _ = sched.step([st.layer_args()], normal.layers, mode="blocking")
+    torch.cuda.synchronize()
+    assert stats["normal_layers"] == 1 and normal.status() == 0 and st.status() == 0
+    b = normal.bufs[0]
+    x, wgu, wd = (b[k].double().cpu() for k in ("x", "w_gu", "w_down"))
+    assert torch.equal(b["x"].view(B, hq, 128), b["out"].bfloat16())
+
+    def close(got, want, mass, what):
+        # one rounding to bf16 (8 significant bits: half a unit in the last place is at most 2^-8 of the
+        # value), and fp32 sums of products of total size `mass`
+        err = (got.double().cpu() - want).abs() - (2.0 ** -8 * want.abs() + 2.0 ** -20 * mass)
+        say(f"  {what}: worst excess {err.max().item():.1e}")
+        assert err.max().item() <= 0, what
+
+    close(b["gu"], x @ wgu.T, x.abs() @ wgu.abs().T, "gu")
+    g, u = b["gu"].double().cpu()[:, :F], b["gu"].double().cpu()[:, F:]
+    close(b["h"], g * torch.sigmoid(g) * u, (g * u).abs(), "h")
+    h = b["h"].double().cpu()
+    close(b["y"], h @ wd.T, h.abs() @ wd.abs().T, "y")
+    sched.destroy()
