@@ -42,6 +42,76 @@ constexpr int kCombineThreads = kHeadDim;
 // 128 floats) stays within 32 KiB, else 4.  Fewer, wider workgroups leave
 // fewer partials for the combine kernel.
 
+// Entries of one 32-token step, and of the shortest split.
+static int32_t split_step(int32_t bs) { return bs >= kChunkTokens ? 1 : kChunkTokens / bs; }
+static int32_t split_least(int32_t bs) { return bs >= 2 * kChunkTokens ? 1 : 2 * kChunkTokens / bs; }
+
+struct SplitArgs {
+    int32_t eps, n_wg;    // host plan: entries per wave, workgroups per (request, KV head)
+    int32_t step, least;  // granularity and least value of eps
+    bool planned;         // share the grid out by the counts
+};
+
+// ---- the split plan ----
+// The host sizes the grid for requests of k_max selected blocks each: n_wg workgroups
+// per (request, KV head), whose W waves take eps entries each.  Counts live on the
+// device; where they differ, that leaves long requests few waves and short ones idle
+// workgroups, so the kernels share the same grid out by the counts: the least eps with
+// which ceil(cnt / (W * eps)) workgroups per request and head fit the grid, and at
+// least the length that would give kTargetWaves waves in all.  Workgroup p is piece
+// (p / Hkv, head p % Hkv) of the requests' pieces in order; its partial is number p.
+// Taken for up to 64 requests (one lane each) when a request may have several
+// workgroups: at 16 requests x 65K tokens with budgets of 317 to 8192 tokens (lognormal
+// around 2048) 58.2 us before, 42.6 with it (188 MB; the split kernel at 5.7 TB/s).  Equal counts
+// keep the host's own split: 8 x 2048 tokens 16.2 us (16.7 with splits numbered before heads, as
+// before), 4 x 8192 at G 8 30.1 (30.4).
+constexpr int kPlanRequests = 64;
+
+struct Piece {
+    int eps, nwg, base;  // entries per wave, workgroups of the request, its first piece
+    int r, wg;
+    int32_t cnt;         // selected blocks of the request (0 if the count is invalid)
+};
+
+// Workgroups of a request of c blocks: at least one, which writes an empty request's output.
+__device__ inline int pieces_of(int c, int per) { return max(1, (c + per - 1) / per); }
+
+// Whether every request has k_max blocks (raw: sel_cnt of request `lane`): the host's split as it is.
+__device__ inline bool equal_counts(int32_t raw, int32_t B, int32_t k_max, int lane) {
+    return __ballot(lane < B && raw != k_max) == 0;
+}
+
+// Plan for piece index pr (of all heads of a request at once); all lanes of a wave take
+// part.  raw: sel_cnt of request `lane` (B <= kPlanRequests).  r < 0: no such piece.
+__device__ inline Piece plan_piece(int pr, int32_t raw, int32_t B, int32_t k_max, int32_t Hkv, int32_t W,
+                                   int32_t eps0, int32_t n_wg0, int32_t step, int32_t least, int lane) {
+    const int c = (lane < B && raw >= 0 && raw <= k_max) ? raw : 0;
+    Piece p;
+    p.eps = eps0;
+    auto pieces = [&](int eps) { return lane < B ? (uint32_t)pieces_of(c, W * eps) : 0u; };
+    const uint32_t total = last_lane(wave_scan((uint32_t)c, 0u, OpAdd()));
+    const int64_t waves = PULSE_ATTN_TARGET_WAVES;
+    int lo = (int)(((int64_t)total * Hkv + waves - 1) / waves);
+    lo = max(least, (lo + step - 1) / step * step);
+    int hi = eps0;  // fits: no request has more than n_wg0 workgroups then
+    while (lo < hi) {
+        const int mid = (lo + hi) / 2 / step * step;
+        if (last_lane(wave_scan(pieces(mid), 0u, OpAdd())) <= (uint32_t)B * (uint32_t)n_wg0) hi = mid;
+        else lo = mid + step;
+    }
+    p.eps = hi;
+    const uint32_t np = pieces(p.eps);
+    const uint32_t incl = wave_scan(np, 0u, OpAdd());
+    const int before = __popcll(__ballot(lane < B && (int)(incl - np) <= pr));
+    p.r = pr < (int)last_lane(incl) ? before - 1 : -1;
+    const int at = max(p.r, 0);
+    p.nwg = __builtin_amdgcn_readlane((int)np, at);
+    p.base = __builtin_amdgcn_readlane((int)(incl - np), at);
+    p.cnt = __builtin_amdgcn_readlane(c, at);
+    p.wg = pr - p.base;
+    return p;
+}
+
 // Attention of one wave over entries [e0, e0 + ne) of request r, KV head h;
 // j_lane is the selected block of entry e0 + lane (loaded by the caller).
 // Leaves the running max (log2 domain) and the lane-group-reduced sum for
@@ -49,8 +119,8 @@ constexpr int kCombineThreads = kHeadDim;
 template <int DT, int BS>
 __device__ inline void attend_split(const uint16_t* __restrict__ q, const uint16_t* __restrict__ pool,
                                     int32_t n_slots, const int32_t* __restrict__ table, int32_t max_blocks,
-                                    int32_t j_lane, int ctx, int32_t Hq, int32_t Hkv, int32_t G,
-                                    int r, int h, int e0, int ne, float scale_log2, int32_t* status, int lane,
+                                    int32_t j_lane, const int32_t* __restrict__ ctx_len, int32_t Hq, int32_t Hkv,
+                                    int32_t G, int r, int h, int ne, float scale_log2, int32_t* status, int lane,
                                     float& m_run, float& l_run, f32x4 (&acc)[8]) {
     using M = Mfma<DT>;
     using vec = typename M::vec;
@@ -61,18 +131,17 @@ __device__ inline void attend_split(const uint16_t* __restrict__ q, const uint16
     m_run = -INFINITY;
     l_run = 0.f;
     if (ne <= 0) return;
-    // entry metadata, one entry per lane (ne <= 64)
+    // entry metadata, one entry per lane (ne <= 64); the table lookup does not wait for the context length
+    const int32_t j = lane < ne ? j_lane : -1;
+    const int32_t sl = (j >= 0 && j < max_blocks) ? table[(size_t)r * max_blocks + j] : -1;
+    const int ctx = ctx_len[r];
     const int64_t n_r = ((int64_t)ctx + BS - 1) / BS;
     int my_slot = -1, my_nv = 0;
     if (lane < ne) {
-        const int32_t j = j_lane;
-        if (j >= 0 && j < n_r && j < max_blocks) {
-            const int32_t sl = table[(size_t)r * max_blocks + j];
-            if (sl >= 0 && sl < n_slots) {
-                my_slot = sl;
-                const int64_t v = (int64_t)ctx - (int64_t)j * BS;
-                my_nv = v >= BS ? BS : (int)v;
-            }
+        if (j < n_r && sl >= 0 && sl < n_slots) {
+            my_slot = sl;
+            const int64_t v = (int64_t)ctx - (int64_t)j * BS;
+            my_nv = v >= BS ? BS : (int)v;
         }
         if (my_slot < 0) report(status, PULSE_ERR_BAD_INDEX);
     }
@@ -189,55 +258,75 @@ __device__ inline void attend_split(const uint16_t* __restrict__ q, const uint16
     l_run += __shfl_xor(l_run, 32);
 }
 
-// grid = (workgroups per (r, h), Hkv, B); W waves per workgroup, wave w owns
-// split W*blockIdx.x + w of eps entries.  Dynamic LDS: O [W][G][128] floats
-// then (m, l) [W][G] float2.
+// grid = (n_wg0 * Hkv, B), numbered in a row: workgroup p is piece p / Hkv of KV head p % Hkv (see the split plan); wave w of a
+// request's workgroup wg owns split W * wg + w of eps entries.  Dynamic LDS: O [W][G][128] floats then
+// (m, l) [W][G] float2.
 template <int DT, int BS, int W>
 __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ pool, int32_t n_slots,
     const int32_t* __restrict__ table, int32_t max_blocks, const int32_t* __restrict__ sel_idx,
-    const int32_t* __restrict__ sel_cnt, int32_t k_max, const int32_t* __restrict__ ctx_len, int32_t Hq,
-    int32_t Hkv, int32_t G, int32_t eps, int32_t n_wg, float scale_log2, float* __restrict__ ws_o,
+    const int32_t* __restrict__ sel_cnt, int32_t k_max, const int32_t* __restrict__ ctx_len, int32_t B, int32_t Hq,
+    int32_t Hkv, int32_t G, SplitArgs sp, float scale_log2, float* __restrict__ ws_o,
     float2* __restrict__ ws_ml, float* __restrict__ out, float* __restrict__ lse, __bf16* __restrict__ x,
     int32_t* status) {
     extern __shared__ float smem[];
     constexpr int kThreads = W * kWave;
     float* s_o = smem;                                                           // [W][G][128]
     float2* s_ml = reinterpret_cast<float2*>(smem + W * G * kHeadDim);  // [W][G]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, grp = lane >> 4;
-    const int wg = blockIdx.x, h = blockIdx.y, r = blockIdx.z;
+    const uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;
+    const int pr = (int)(id / (uint32_t)Hkv), h = (int)(id % (uint32_t)Hkv);
+
+    // this wave's selected blocks (one per lane) are loaded with the counts they depend on, at the place
+    // they have when all counts are equal: one memory round trip fewer before the first K load
+    Piece p;
+    p.r = pr / sp.n_wg;
+    p.wg = pr % sp.n_wg;
+    p.eps = sp.eps;
+    const bool planned = sp.planned;
+    auto load_j = [&]() {
+        const int e = (p.wg * W + wave) * p.eps + lane;
+        return (lane < p.eps && e < k_max) ? sel_idx[(size_t)p.r * k_max + e] : -1;
+    };
+    int32_t j_lane = load_j();
+    if (planned) {
+        const int32_t raw = lane < B ? sel_cnt[lane] : 0;
+        if (id == 0 && wave == 0 && (raw < 0 || raw > k_max)) report(status, PULSE_ERR_BAD_INDEX);
+        p.cnt = k_max;
+        p.nwg = sp.n_wg;
+        if (!equal_counts(raw, B, k_max, lane)) {
+            const int r0 = p.r, wg0 = p.wg;
+            p = plan_piece(pr, raw, B, k_max, Hkv, W, sp.eps, sp.n_wg, sp.step, sp.least, lane);
+            if (p.r < 0) return;  // fewer pieces than workgroups
+            if (p.r != r0 || p.wg != wg0 || p.eps != sp.eps) j_lane = load_j();
+        }
+    } else {
+        p.cnt = sel_cnt[p.r];
+        if (p.cnt < 0 || p.cnt > k_max) {
+            if (tid == 0) report(status, PULSE_ERR_BAD_INDEX);
+            p.cnt = 0;
+        }
+        p.nwg = pieces_of(p.cnt, W * p.eps);
+        if (p.wg >= p.nwg) return;
+    }
+    const int r = p.r;
     float* out_rh = out + ((size_t)r * Hq + (size_t)h * G) * kHeadDim;
     float* lse_rh = lse ? lse + (size_t)r * Hq + (size_t)h * G : nullptr;
     __bf16* x_rh = x ? x + ((size_t)r * Hq + (size_t)h * G) * kHeadDim : nullptr;
-
-    // this wave's selected blocks (one per lane) are loaded with the count they
-    // depend on, not after it: one memory round trip fewer before the first K load
-    const int s = wg * W + wave;
-    const int e0 = s * eps;
-    const int32_t j_lane = (lane < eps && e0 + lane < k_max) ? sel_idx[(size_t)r * k_max + e0 + lane] : -1;
-    int32_t cnt = sel_cnt[r];
-    if (cnt < 0 || cnt > k_max) {
-        if (tid == 0) report(status, PULSE_ERR_BAD_INDEX);
-        cnt = 0;
-    }
-    const int ns = (cnt + eps - 1) / eps;                // non-empty splits of (r, h)
-    const int nwg = (ns + W - 1) / W;  // workgroups with work
-    if (wg >= nwg) {
-        if (cnt == 0 && wg == 0) {  // empty selection: out = 0, lse = -inf
-            for (int i = tid; i < G * kHeadDim; i += kThreads) {
-                out_rh[i] = 0.f;
-                if (x_rh) x_rh[i] = (__bf16)0.f;
-            }
-            if (lse_rh && tid < G) lse_rh[tid] = -INFINITY;
+    if (p.cnt == 0) {  // empty selection: out = 0, lse = -inf
+        for (int i = tid; i < G * kHeadDim; i += kThreads) {
+            out_rh[i] = 0.f;
+            if (x_rh) x_rh[i] = (__bf16)0.f;
         }
+        if (lse_rh && tid < G) lse_rh[tid] = -INFINITY;
         return;
     }
-    const int ne = min(e0 + eps, cnt) - e0;
+    const int ne = min(p.eps, p.cnt - (p.wg * W + wave) * p.eps);
     float m_run, l_run;
     f32x4 acc[8];
-    attend_split<DT, BS>(q, pool, n_slots, table, max_blocks, j_lane, ctx_len[r], Hq, Hkv, G, r,
-                         h, e0, ne, scale_log2, status, lane, m_run, l_run, acc);
+    attend_split<DT, BS>(q, pool, n_slots, table, max_blocks, j_lane, ctx_len, Hq, Hkv, G, r, h, ne, scale_log2,
+                         status, lane, m_run, l_run, acc);
     // wave partials to LDS
     if (grp == 0 && col < G) s_ml[wave * G + col] = make_float2(m_run, l_run);
 #pragma unroll
@@ -251,7 +340,7 @@ __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
     }
     __syncthreads();
     // merge the W waves: thread handles outputs (g, c) = (idx / 128, idx % 128)
-    const size_t unit = ((size_t)r * Hkv + h) * n_wg + wg;
+    const size_t unit = id;
     for (int idx = tid; idx < G * kHeadDim; idx += kThreads) {
         const int g = idx / kHeadDim, c = idx % kHeadDim;
         float Mx = -INFINITY;
@@ -267,7 +356,7 @@ __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
                 a += s_o[(w * G + g) * kHeadDim + c] * wt;
             }
         }
-        if (nwg == 1) {
+        if (p.nwg == 1) {
             const float o = Mx == -INFINITY ? 0.f : a / L;
             out_rh[idx] = o;
             if (x_rh) x_rh[idx] = (__bf16)o;
@@ -286,35 +375,47 @@ __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
 // kernel.
 __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
     const float* __restrict__ ws_o, const float2* __restrict__ ws_ml, const int32_t* __restrict__ sel_cnt,
-    int32_t k_max, int32_t Hq, int32_t Hkv, int32_t G, int32_t eps, int32_t n_wg, int32_t waves,
+    int32_t k_max, int32_t B, int32_t Hq, int32_t Hkv, int32_t G, SplitArgs sp, int32_t waves,
     float* __restrict__ out, float* __restrict__ lse, __bf16* __restrict__ x) {
     const int c = threadIdx.x, g = blockIdx.x, h = blockIdx.y, r = blockIdx.z;
-    const size_t u0 = ((size_t)r * Hkv + h) * n_wg;
-    const float2* ml = ws_ml + u0 * G + g;                  // stride G
-    const float* po = ws_o + (u0 * G + g) * kHeadDim + c;   // stride G * 128
-    // the first 8 partials are loaded before the request's workgroup count is
-    // known (n_wg bounds it); entries past that count are discarded below
+    // piece i of this (request, head) is partial (base + i) * Hkv + h; with equal counts base = r * n_wg.
+    // The first 8 are loaded there before the counts are known, and again if the base differs.
+    const float2* ml = ws_ml + (size_t)h * G + g;
+    const float* po = ws_o + ((size_t)h * G + g) * kHeadDim + c;
     float2 mlv[8];
     float ov[8];
+    auto load8 = [&](int first, int n) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        mlv[i] = i < n_wg ? ml[(size_t)i * G] : make_float2(-INFINITY, 0.f);
-        ov[i] = i < n_wg ? po[(size_t)i * G * kHeadDim] : 0.f;
+        for (int i = 0; i < 8; ++i) {
+            const size_t u = (size_t)(first + i) * Hkv * G;
+            mlv[i] = i < n ? ml[u] : make_float2(-INFINITY, 0.f);
+            ov[i] = i < n ? po[u * kHeadDim] : 0.f;
+        }
+    };
+    load8(r * sp.n_wg, sp.n_wg);
+    int nwg, base = r * sp.n_wg;
+    if (sp.planned) {
+        const int lane = c & 63;
+        const int32_t raw = lane < B ? sel_cnt[lane] : 0;
+        nwg = sp.n_wg;
+        if (!equal_counts(raw, B, k_max, lane)) {
+            const Piece p = plan_piece(0, raw, B, k_max, Hkv, waves, sp.eps, sp.n_wg, sp.step, sp.least, lane);
+            // the request's own pieces: those of lane r
+            const int cl = (raw >= 0 && raw <= k_max) ? raw : 0;
+            const uint32_t np = (uint32_t)pieces_of(cl, waves * p.eps);
+            nwg = __builtin_amdgcn_readlane((int)np, r);
+            base = (int)last_lane(wave_scan(lane < r ? np : 0u, 0u, OpAdd()));
+        }
+    } else {
+        const int32_t cnt = sel_cnt[r];
+        nwg = (cnt < 0 || cnt > k_max) ? 1 : pieces_of(cnt, waves * sp.eps);
     }
-    int32_t cnt = sel_cnt[r];
-    if (cnt < 0 || cnt > k_max) cnt = 0;
-    const int ns = (cnt + eps - 1) / eps;
-    const int nwg = (ns + waves - 1) / waves;
     if (nwg <= 1) return;
+    if (base != r * sp.n_wg || nwg > sp.n_wg) load8(base, nwg);
     float m_run = -INFINITY, L = 0.f, a = 0.f;
     for (int w0 = 0; w0 < nwg; w0 += 8) {
         if (w0 > 0) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const bool ok = w0 + i < nwg;
-                mlv[i] = ok ? ml[(size_t)(w0 + i) * G] : make_float2(-INFINITY, 0.f);
-                ov[i] = ok ? po[(size_t)(w0 + i) * G * kHeadDim] : 0.f;
-            }
+            load8(base + w0, nwg - w0);
         } else {
 #pragma unroll
             for (int i = 0; i < 8; ++i)
@@ -348,12 +449,12 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
 }
 
 AttnPlan attn_plan(int32_t B, int32_t Hkv, int32_t k_max, int32_t bs) {
-    // entries per 32-token step; a split covers >= 2 steps, <= 64 entries
-    const int32_t step = bs >= kChunkTokens ? 1 : kChunkTokens / bs;
+    // a split covers whole 32-token steps, at least two, and at most 64 entries
+    const int32_t step = split_step(bs);
     const int64_t units = (int64_t)B * Hkv;
     const int64_t target_waves = PULSE_ATTN_TARGET_WAVES;  // one round at 2 resident waves per SIMD on 256 CUs
     int64_t want = units > 0 ? (target_waves + units - 1) / units : 1;
-    int64_t min_entries = (bs >= 2 * kChunkTokens) ? 1 : (2 * kChunkTokens) / bs;
+    const int64_t min_entries = split_least(bs);
     int64_t max_split = (k_max + min_entries - 1) / min_entries;
     if (want > max_split) want = max_split;
     if (want < 1) want = 1;
@@ -371,12 +472,12 @@ AttnPlan attn_plan(int32_t B, int32_t Hkv, int32_t k_max, int32_t bs) {
 template <int DT, int BS, int W>
 static void launch_attn_t(dim3 grid, size_t lds, hipStream_t st, hipEvent_t done, const void* q, const void* pool,
                           int32_t n_slots, const int32_t* table, int32_t max_blocks, const int32_t* sel_idx,
-                          const int32_t* sel_cnt, int32_t k_max, const int32_t* ctx_len, int32_t Hq, int32_t Hkv,
-                          int32_t G, int32_t eps, int32_t n_wg, float scale_log2, float* ws_o, float2* ws_ml,
+                          const int32_t* sel_cnt, int32_t k_max, const int32_t* ctx_len, int32_t B, int32_t Hq,
+                          int32_t Hkv, int32_t G, const SplitArgs& sp, float scale_log2, float* ws_o, float2* ws_ml,
                           float* out, float* lse, __bf16* x, int32_t* status) {
     launch_timed(attn_splitk_kernel<DT, BS, W>, grid, dim3(W * kWave), (uint32_t)lds, st, nullptr, done,
                  (const uint16_t*)q, (const uint16_t*)pool, n_slots, table, max_blocks, sel_idx, sel_cnt, k_max,
-                 ctx_len, Hq, Hkv, G, eps, n_wg, scale_log2, ws_o, ws_ml, out, lse, x, status);
+                 ctx_len, B, Hq, Hkv, G, sp, scale_log2, ws_o, ws_ml, out, lse, x, status);
 }
 
 hipError_t launch_attention(const pulse_shape& s, const void* q, const void* pool, int32_t n_slots,
@@ -389,15 +490,20 @@ hipError_t launch_attention(const pulse_shape& s, const void* q, const void* poo
     const AttnPlan p = attn_plan(B, Hkv, k_max, s.block_size);
     const int W = attn_waves(G);
     const int32_t n_wg = (p.n_split + W - 1) / W;
-    dim3 grid((unsigned)n_wg, (unsigned)Hkv, (unsigned)B);
+    const dim3 grid((unsigned)n_wg * (unsigned)Hkv, (unsigned)B);  // numbered in a row
+    SplitArgs sp;
+    sp.eps = p.entries_per_split;
+    sp.n_wg = n_wg;
+    sp.step = split_step(s.block_size);
+    sp.least = split_least(s.block_size);
+    sp.planned = n_wg > 1 && B <= kPlanRequests && k_max <= (1 << 24);  // the counts add up in 32 bits
     const size_t lds = sizeof(float) * W * G * kHeadDim + sizeof(float2) * W * G;
     const float scale_log2 = sm_scale * 1.4426950408889634f;
     // stop event of the split-K kernel: split_done, or `done` when no combine follows it
     const hipEvent_t splitk_stop = split_done ? split_done : (n_wg <= 1 ? done : nullptr);
 #define PULSE_ATTN(DT, BS, W)                                                                                        \
     launch_attn_t<DT, BS, W>(grid, lds, st, splitk_stop, q, pool, n_slots, table, max_blocks, sel_idx, sel_cnt,     \
-                             k_max, ctx_len,                                                                        \
-                             Hq, Hkv, G, p.entries_per_split, n_wg, scale_log2, ws_o, ws_ml, out, lse, x, status)
+                             k_max, ctx_len, B, Hq, Hkv, G, sp, scale_log2, ws_o, ws_ml, out, lse, x, status)
 #define PULSE_ATTN_W(DT, BS) \
     if (W == 8) PULSE_ATTN(DT, BS, 8); else PULSE_ATTN(DT, BS, 4)
     if (s.dtype == PULSE_BF16) {
@@ -415,8 +521,8 @@ hipError_t launch_attention(const pulse_shape& s, const void* q, const void* poo
     if (e != hipSuccess) return e;
     if (n_wg <= 1) return (done && split_done) ? hipEventRecord(done, st) : hipSuccess;
     launch_timed(attn_combine_kernel, dim3((unsigned)G, (unsigned)Hkv, (unsigned)B), dim3(kCombineThreads), 0u, st,
-                 nullptr, done, (const float*)ws_o, (const float2*)ws_ml, sel_cnt, k_max, Hq, Hkv, G,
-                 p.entries_per_split, n_wg, W, out, lse, x);
+                 nullptr, done, (const float*)ws_o, (const float2*)ws_ml, sel_cnt, k_max, B, Hq, Hkv, G, sp, W, out, lse,
+                 x);
     return hipGetLastError();
 }
 

@@ -45,6 +45,29 @@ __device__ inline void report(int32_t* status, int32_t code) {
     if (status) atomicCAS(status, 0, code);
 }
 
+// ---- wave scans ------------------------------------------------------------
+
+// Inclusive scan of x over the 64 lanes of a wave with `op`, in registers
+// (DPP row shifts within 16-lane rows, then row broadcasts of lanes 15 and
+// 31); lanes without a source combine with `identity`.
+template <typename Op>
+__device__ inline uint32_t wave_scan(uint32_t x, uint32_t identity, Op op) {
+    const int id = (int)identity;
+    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)x, 0x111, 0xF, 0xF, false));  // row_shr:1
+    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)x, 0x112, 0xF, 0xF, false));  // row_shr:2
+    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)x, 0x114, 0xF, 0xF, false));  // row_shr:4
+    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)x, 0x118, 0xF, 0xF, false));  // row_shr:8
+    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)x, 0x142, 0xA, 0xF, false));  // row_bcast:15
+    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)x, 0x143, 0xC, 0xF, false));  // row_bcast:31
+    return x;
+}
+struct OpAdd { __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a + b; } };
+struct OpMin { __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a < b ? a : b; } };
+struct OpMax { __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a > b ? a : b; } };
+
+// Value of lane 63 (the wave-wide result of an inclusive scan), in every lane.
+__device__ inline uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
+
 // ---- 16-bit element helpers ------------------------------------------------
 
 // Order-preserving map of a sign-magnitude 16-bit float pattern onto uint16:

@@ -38,27 +38,6 @@ constexpr int kTile = kRounds * kSelThreads;        // blocks per tile; one-tile
 constexpr int kEntries = kRounds * kSelWaves;       // (round, wave) entries of a tile: two per lane
 constexpr int kWords = kRounds / 4;                 // words of per-round byte counts
 
-// Inclusive scan of x over the 64 lanes of a wave with `op`, in registers
-// (DPP row shifts within 16-lane rows, then row broadcasts of lanes 15 and
-// 31); lanes without a source combine with `identity`.
-template <typename Op>
-__device__ inline uint32_t wave_scan(uint32_t x, uint32_t identity, Op op) {
-    const int id = (int)identity;
-    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)x, 0x111, 0xF, 0xF, false));  // row_shr:1
-    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)x, 0x112, 0xF, 0xF, false));  // row_shr:2
-    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)x, 0x114, 0xF, 0xF, false));  // row_shr:4
-    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)x, 0x118, 0xF, 0xF, false));  // row_shr:8
-    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)x, 0x142, 0xA, 0xF, false));  // row_bcast:15
-    x = op(x, (uint32_t)__builtin_amdgcn_update_dpp(id, (int)x, 0x143, 0xC, 0xF, false));  // row_bcast:31
-    return x;
-}
-struct OpAdd { __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a + b; } };
-struct OpMin { __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a < b ? a : b; } };
-struct OpMax { __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a > b ? a : b; } };
-
-// Value of lane 63 (the wave-wide result of an inclusive scan), in every lane.
-__device__ inline uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
-
 // Bits 0..3 of x as the bytes 0..3 of a word (0 or 1 each): the four shifted
 // copies x << 7i land on distinct bit positions, so the product has no carries.
 __device__ inline uint32_t spread_bytes(uint32_t x) { return ((x & 0xFu) * 0x00204081u) & 0x01010101u; }

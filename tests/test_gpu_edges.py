@@ -111,3 +111,51 @@ def test_normal_layer_edges(B, F, hq, hkv, ctx):
     h = b["h"].double().cpu()
     close(b["y"], h @ wd.T, h.abs() @ wd.abs().T, "y")
     sched.destroy()
+
+
+# Selected blocks per request around the shares of the split plan: equal, one long request among short and
+# empty ones, the plan's limit of 64 requests and one past it, many heads per KV head (4-wave workgroups).
+PLAN_CASES = [
+    ([128] * 4, 8, 2, 16, "bf16"), ([300, 0, 1, 2, 5], 8, 2, 16, "bf16"), ([0, 0, 0, 260], 4, 1, 16, "f16"),
+    ([1, 97, 98, 99, 513], 32, 8, 16, "bf16"), ([40] * 63 + [200], 2, 1, 16, "f16"),
+    ([40] * 64 + [200], 2, 1, 16, "bf16"), ([7, 150, 33], 32, 2, 32, "bf16"), ([3, 260, 0, 31], 12, 1, 64, "f16"),
+    ([0, 0], 4, 2, 16, "bf16"), ([9] * 40 + [800], 8, 8, 32, "bf16"),
+]
+
+
+@pytest.mark.parametrize("cnt,hq,hkv,bs,dt", PLAN_CASES)
+def test_attention_split_plan(cnt, hq, hkv, bs, dt):
+    say(f"\n[gpu] split plan cnt={cnt[:5]}.. hq={hq} hkv={hkv} bs={bs}")
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(sum(cnt) + bs + hq)
+    dtype = torch.bfloat16 if dt == "bf16" else torch.float16
+    B, G, k_max = len(cnt), hq // hkv, max(1, max(cnt))
+    ctx = [(c + 3) * bs - (r % bs) for r, c in enumerate(cnt)]  # the last block is partial
+    pool, table, ctx_len, n, mb = _paged(ctx, hkv, bs, dtype, gen)
+    q = torch.randn((B, hq, D), generator=gen, device=DEV, dtype=dtype)
+    sel = torch.full((B, k_max), -1, dtype=torch.int32, device=DEV)
+    for r, c in enumerate(cnt):  # the last c blocks
+        sel[r, :c] = torch.arange(n[r] - c, n[r], dtype=torch.int32, device=DEV)
+    sel_cnt = torch.tensor(cnt, dtype=torch.int32, device=DEV)
+    sh = P.make_shape(hq, hkv, D, bs, P.PULSE_BF16 if dt == "bf16" else P.PULSE_F16)
+    nb = P.pulse_workspace_bytes(sh, B, k_max, 0)
+    ws = torch.full((nb,), 255, dtype=torch.uint8, device=DEV)  # NaN patterns: every partial read was written
+    out = torch.full((B, hq, D), float("nan"), device=DEV)
+    lse = torch.full((B, hq), float("nan"), device=DEV)
+    st = torch.zeros(1, dtype=torch.int32, device=DEV)
+    P.pulse_sparse_decode_attn(sh, q, pool, pool.shape[0], table, mb, sel, sel_cnt, k_max, ctx_len, B, D ** -0.5, out,
+                               lse, st, ws, nb)
+    assert st.item() == 0
+    for r, c in enumerate(cnt):
+        if c == 0:
+            assert (out[r] == 0).all() and (lse[r] == -math.inf).all()
+            continue
+        b = pool[table[r, n[r] - c: n[r]].long()]
+        ok = torch.arange((n[r] - c) * bs, n[r] * bs, device=DEV) < ctx[r]
+        for h in range(hkv):
+            K = b[:, 0, h].reshape(-1, D)[ok].double()
+            V = b[:, 1, h].view(-1, D, bs).transpose(1, 2).reshape(-1, D)[ok].double()
+            s = q[r, h * G:(h + 1) * G].double() @ K.T / math.sqrt(D)
+            # probabilities in two 16-bit parts (2^-16) and fp32 sums: 2^-14 of the values' size is well above both
+            assert (out[r, h * G:(h + 1) * G] - torch.softmax(s, 1) @ V).abs().max() < 2.0 ** -14 * 5, (r, h)
+            assert (lse[r, h * G:(h + 1) * G] - torch.logsumexp(s, 1)).abs().max() < 1e-5, (r, h)
