@@ -26,23 +26,40 @@ __device__ inline int find_request(const int64_t* blk_off, int32_t B, int64_t b)
     return lo;
 }
 
-// One wave per block: lane = (token group tg in 0..3, 8-channel slice).
+typedef __attribute__((ext_vector_type(2))) int16_t s16x2;
+
+// Two 16-bit float patterns as signed integers of the same order (-0 just below +0); its own inverse.
+__device__ inline s16x2 order16(s16x2 x) { return x ^ ((x >> 15) & (int16_t)0x7FFF); }
+
+// One wave per block, lane = (token group tg in 0..3, 8-channel slice).  Bound by HBM (or
+// the host link): 256 bytes per token and 512 per block.  The keys' addresses do not depend
+// on the request, so the whole block is loaded first (BS / 4 loads of 16 bytes in flight per
+// lane) and the request is looked up meanwhile; rows past the context are left out of the
+// minimum and maximum.  Both are taken on packed pairs: with one value per register the
+// vector instructions bound the kernel.  8 x 32K tokens, 8 KV heads (73 MB): 21.2 us with
+// both the look-up first and single values, 15.9 now (4.6 TB/s).
+template <int BS>
 __global__ __launch_bounds__(256) void build_digests_kernel(const uint16_t* __restrict__ kv,
                                                             const int64_t* __restrict__ blk_off,
                                                             const int32_t* __restrict__ ctx_len, int32_t B,
-                                                            int64_t total_blocks, int32_t Hkv, int32_t bs,
-                                                            int32_t kv_head, uint16_t* __restrict__ digests,
-                                                            int32_t* status) {
+                                                            int64_t total_blocks, int32_t Hkv, int32_t kv_head,
+                                                            uint16_t* __restrict__ digests, int32_t* status) {
+    constexpr int R = BS / 4;  // rows per lane
     const int lane = threadIdx.x & 63;
-    const int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int64_t b = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (b >= total_blocks) return;
     const int c8 = (lane & 15) * 8;
     const int tg = lane >> 4;
-    u32x4* dst = reinterpret_cast<u32x4*>(digests + b * 2 * kHeadDim);
+    const size_t E = (size_t)2 * Hkv * BS * kHeadDim;
+    const uint16_t* K = kv + (size_t)b * E + (size_t)kv_head * BS * kHeadDim + tg * kHeadDim + c8;
+    u32x4 v[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) v[i] = *reinterpret_cast<const u32x4*>(K + (size_t)4 * i * kHeadDim);
     const int r = find_request(blk_off, B, b);
     const int64_t j = b - blk_off[r];
-    const int64_t nv64 = (int64_t)ctx_len[r] - j * bs;
-    const int nv = nv64 >= bs ? bs : (int)nv64;
+    const int64_t nv64 = (int64_t)ctx_len[r] - j * BS;
+    const int nv = nv64 >= BS ? BS : (int)nv64;
+    u32x4* dst = reinterpret_cast<u32x4*>(digests + b * 2 * kHeadDim);
     if (j < 0 || b >= blk_off[r + 1] || nv <= 0) {
         if (lane == 0) report(status, PULSE_ERR_BAD_INDEX);
         if (tg == 0) {
@@ -51,33 +68,35 @@ __global__ __launch_bounds__(256) void build_digests_kernel(const uint16_t* __re
         }
         return;
     }
-    const size_t E = (size_t)2 * Hkv * bs * kHeadDim;
-    const uint16_t* K = kv + (size_t)b * E + (size_t)kv_head * bs * kHeadDim;
-    uint32_t mn[8], mx[8];
+    s16x2 mn[4], mx[4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) { mn[i] = 0xFFFFu; mx[i] = 0u; }
-    for (int t = tg; t < nv; t += 4) {
-        u32x4 v = *reinterpret_cast<const u32x4*>(K + (size_t)t * kHeadDim + c8);
+    for (int p = 0; p < 4; ++p) { mn[p] = (int16_t)0x7FFF; mx[p] = (int16_t)0x8000; }
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            uint32_t k = key16((v[i >> 1] >> (16 * (i & 1))) & 0xFFFFu);
-            mn[i] = min(mn[i], k);
-            mx[i] = max(mx[i], k);
+    for (int t = 0; t < R; ++t) {
+        const bool in = nv == BS || tg + 4 * t < nv;
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            const uint32_t two = v[t][p];  // (a bit cast of the element itself would read element 0)
+            const s16x2 k = order16(__builtin_bit_cast(s16x2, two));
+            mn[p] = __builtin_elementwise_min(mn[p], in ? k : mn[p]);
+            mx[p] = __builtin_elementwise_max(mx[p], in ? k : mx[p]);
         }
     }
 #pragma unroll
     for (int off = 16; off <= 32; off <<= 1)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            mn[i] = min(mn[i], (uint32_t)__shfl_xor((int)mn[i], off));
-            mx[i] = max(mx[i], (uint32_t)__shfl_xor((int)mx[i], off));
+        for (int p = 0; p < 4; ++p) {
+            mn[p] = __builtin_elementwise_min(
+                mn[p], __builtin_bit_cast(s16x2, __shfl_xor(__builtin_bit_cast(int, mn[p]), off)));
+            mx[p] = __builtin_elementwise_max(
+                mx[p], __builtin_bit_cast(s16x2, __shfl_xor(__builtin_bit_cast(int, mx[p]), off)));
         }
     if (tg == 0) {
         u32x4 omn, omx;
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-            omn[p] = unkey16(mn[2 * p]) | (unkey16(mn[2 * p + 1]) << 16);
-            omx[p] = unkey16(mx[2 * p]) | (unkey16(mx[2 * p + 1]) << 16);
+            omn[p] = __builtin_bit_cast(uint32_t, order16(mn[p]));
+            omx[p] = __builtin_bit_cast(uint32_t, order16(mx[p]));
         }
         dst[c8 / 8] = omn;
         dst[16 + c8 / 8] = omx;
@@ -213,9 +232,14 @@ hipError_t launch_build_digests(const pulse_shape& s, const void* kv, const int6
                                 const int32_t* ctx_len, int32_t B, int64_t total_blocks, int32_t kv_head,
                                 void* digests, int32_t* status, hipStream_t st) {
     if (total_blocks == 0) return hipSuccess;
-    dim3 grid((unsigned)((total_blocks + 3) / 4));
-    hipLaunchKernelGGL(build_digests_kernel, grid, dim3(256), 0, st, (const uint16_t*)kv, blk_off, ctx_len, B,
-                       total_blocks, s.num_kv_heads, s.block_size, kv_head, (uint16_t*)digests, status);
+#define PULSE_DIGEST(BS)                                                                                          \
+    hipLaunchKernelGGL(build_digests_kernel<BS>, dim3((unsigned)((total_blocks + 3) / 4)), dim3(256), 0, st,     \
+                       (const uint16_t*)kv, blk_off, ctx_len, B, total_blocks, s.num_kv_heads, kv_head,          \
+                       (uint16_t*)digests, status)
+    if (s.block_size == 16) PULSE_DIGEST(16);
+    else if (s.block_size == 32) PULSE_DIGEST(32);
+    else PULSE_DIGEST(64);
+#undef PULSE_DIGEST
     return hipGetLastError();
 }
 

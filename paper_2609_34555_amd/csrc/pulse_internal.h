@@ -70,11 +70,6 @@ __device__ inline uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_am
 
 // ---- 16-bit element helpers ------------------------------------------------
 
-// Order-preserving map of a sign-magnitude 16-bit float pattern onto uint16:
-// increasing values give increasing keys, and -0 sorts just below +0.
-__device__ inline uint32_t key16(uint32_t x) { return (x & 0x8000u) ? (~x & 0xFFFFu) : (x | 0x8000u); }
-__device__ inline uint32_t unkey16(uint32_t k) { return (k & 0x8000u) ? (k & 0x7FFFu) : (~k & 0xFFFFu); }
-
 // Order-preserving map of fp32 onto uint32 (both zeros map to the key of +0).
 __device__ inline uint32_t key32(float s) {
     s = s + 0.0f;  // -0 -> +0
