@@ -188,14 +188,11 @@ pulse_status pulse_select_average(const pulse_shape* shape, const void* q, const
     if (st != PULSE_OK || B == 0) return st;
     PULSE_REQUIRE(ws && ws_bytes >= pulse_average_workspace_bytes(shape, B, k_max, total_blocks),
                   PULSE_ERR_WORKSPACE);
-    const int32_t H = shape->num_kv_heads;
-    float* sc = at<float>(ws, 0);
-    float* avg = scores ? scores : at<float>(ws, align_up(sizeof(float) * (size_t)H * (size_t)total_blocks));
+    const size_t heads = sizeof(float) * (size_t)shape->num_kv_heads * (size_t)total_blocks;
+    float* avg = scores ? scores : at<float>(ws, align_up(heads));
     hipStream_t hs = (hipStream_t)stream;
-    hipError_t e = launch_score(*shape, q, head_digests, blk_off, B, total_blocks, 0, n_sink_blocks, n_local_blocks,
-                                sc, H, hs);
-    if (e != hipSuccess) return PULSE_ERR_HIP;
-    e = launch_average_scores(sc, total_blocks, H, avg, hs);
+    hipError_t e = launch_average_scores(*shape, q, head_digests, blk_off, B, total_blocks, n_sink_blocks,
+                                         n_local_blocks, avg, at<float>(ws, 0), hs);
     if (e != hipSuccess) return PULSE_ERR_HIP;
     e = launch_select(blk_off, B, total_blocks, avg, k_mid, n_sink_blocks, n_local_blocks, k_max, sel_idx, sel_cnt,
                       nullptr, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, dev_status, 1, hs);

@@ -228,6 +228,100 @@ __global__ __launch_bounds__(256) void score_kernel(const uint16_t* __restrict__
     }
 }
 
+// Scores averaged over the KV heads (Average selection), in one launch for small sets.  A
+// workgroup scores every head of bpw consecutive blocks: its 16-lane groups take (block,
+// head) pairs, block-major, with score_kernel's loads and sums, and the heads' scores of a
+// block are added in ascending order from LDS.
+template <int DT, int G>
+__global__ __launch_bounds__(256) void score_average_kernel(const uint16_t* __restrict__ q,
+                                                            const uint16_t* __restrict__ digests,
+                                                            const int64_t* __restrict__ blk_off, int32_t B,
+                                                            int64_t total_blocks, int32_t Hq, int32_t H, int32_t bpw,
+                                                            int32_t n_sink, int32_t n_local,
+                                                            float* __restrict__ scores) {
+    extern __shared__ int64_t s_off[];                        // [B + 1]
+    float* s_sc = reinterpret_cast<float*>(s_off + B + 1);   // [bpw][H]
+    const int sub = threadIdx.x & 15;
+    const int gi = threadIdx.x >> 4;
+    const int64_t b0 = (int64_t)blockIdx.x * bpw;
+    const int pairs = (int)min((int64_t)bpw, total_blocks - b0) * H;
+    for (int p0 = 0; p0 < pairs; p0 += 16) {
+        const int p = min(p0 + gi, pairs - 1);  // groups past the last pair repeat it
+        const int h = p % H;
+        const int64_t b = b0 + p / H;
+        const u32x4* dg =
+            reinterpret_cast<const u32x4*>(digests + ((size_t)h * total_blocks + (size_t)b) * 2 * kHeadDim);
+        const u32x4 dmn = dg[sub], dmx = dg[16 + sub];
+        u32x4 qv[G];
+        auto load_q = [&](int r) {
+            const uint16_t* qr = q + ((size_t)r * Hq + (size_t)h * G) * kHeadDim + sub * 8;
+#pragma unroll
+            for (int g = 0; g < G; ++g) qv[g] = *reinterpret_cast<const u32x4*>(qr + (size_t)g * kHeadDim);
+        };
+        // the rows of the request the block has if all are equally long, with the digests
+        const int guess = min((int)(b * B / total_blocks), B - 1);
+        load_q(guess);
+        if (p0 == 0) {
+            for (int i = threadIdx.x; i <= B; i += 256) s_off[i] = blk_off[i];
+            __syncthreads();
+        }
+        if (b < s_off[guess] || b >= s_off[guess + 1]) load_q(find_request_lds(s_off, B, b));
+        float acc = 0.f;
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t qw = qv[g][c];
+                const uint32_t qm = ~(((qw & 0x80008000u) >> 15) * 0xFFFFu);
+                acc = dot2<DT>(qw, (dmx[c] & qm) | (dmn[c] & ~qm), acc);
+            }
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) acc += __shfl_xor(acc, off);
+        if (sub == 0) s_sc[p] = acc / (float)G;
+    }
+    __syncthreads();
+    const float inv = 1.f / (float)H;
+    for (int t = threadIdx.x; t * H < pairs; t += 256) {
+        const int64_t b = b0 + t;
+        const int r = find_request_lds(s_off, B, b);
+        const int64_t j = b - s_off[r], n = s_off[r + 1] - s_off[r];
+        if (j < n_sink || j >= n - n_local) continue;  // forced blocks are not scored
+        float s = 0.f;
+        for (int h = 0; h < H; ++h) s += s_sc[t * H + h];
+        scores[b] = s * inv;
+    }
+}
+
+// avg[b] = (1/H) * sum_h sc[h][b], heads summed in ascending order, eight of them in flight
+// at a time (one after the other: 4.8 us on 8 x 65536 scores).  Entries that were not scored
+// (forced blocks) are not written.
+__global__ __launch_bounds__(256) void average_scores_kernel(const float* __restrict__ sc,
+                                                             const int64_t* __restrict__ blk_off, int32_t B,
+                                                             int64_t total_blocks, int32_t H, int32_t n_sink,
+                                                             int32_t n_local, float* __restrict__ avg) {
+    extern __shared__ int64_t s_off[];
+    const int64_t b = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const float* p = sc + min(b, total_blocks - 1);
+    float s = 0.f, v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = p[(size_t)min(i, H - 1) * total_blocks];
+    for (int i = threadIdx.x; i <= B; i += 256) s_off[i] = blk_off[i];
+    __syncthreads();
+    for (int h0 = 0; h0 < H; h0 += 8) {
+        if (h0 > 0) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = p[(size_t)min(h0 + i, H - 1) * total_blocks];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (h0 + i < H) s += v[i];
+    }
+    if (b >= total_blocks) return;
+    const int r = find_request_lds(s_off, B, b);
+    const int64_t j = b - s_off[r], n = s_off[r + 1] - s_off[r];
+    if (j >= n_sink && j < n - n_local) avg[b] = s * (1.f / (float)H);
+}
+
 hipError_t launch_build_digests(const pulse_shape& s, const void* kv, const int64_t* blk_off,
                                 const int32_t* ctx_len, int32_t B, int64_t total_blocks, int32_t kv_head,
                                 void* digests, int32_t* status, hipStream_t st) {
@@ -261,6 +355,16 @@ static void launch_score_t(int32_t heads, hipStream_t st, hipEvent_t ev0, hipEve
     }
 }
 
+template <int DT, int G>
+static void launch_average_t(hipStream_t st, const void* q, const void* digests, const int64_t* blk_off, int32_t B,
+                             int64_t total, int32_t Hq, int32_t H, int32_t n_sink, int32_t n_local, float* scores) {
+    const int32_t bpw = H < 16 ? 16 / H : 1;
+    const uint32_t lds = (uint32_t)(sizeof(int64_t) * ((size_t)B + 1) + sizeof(float) * (size_t)bpw * H);
+    hipLaunchKernelGGL((score_average_kernel<DT, G>), dim3((unsigned)((total + bpw - 1) / bpw)), dim3(256), lds, st,
+                       (const uint16_t*)q, (const uint16_t*)digests, blk_off, B, total, Hq, H, bpw, n_sink, n_local,
+                       scores);
+}
+
 template <int DT>
 static void launch_score_dt(int G, int32_t heads, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1, const void* q,
                             const void* digests, const int64_t* blk_off, int32_t B, int64_t total, int32_t Hq,
@@ -278,6 +382,54 @@ static void launch_score_dt(int G, int32_t heads, hipStream_t st, hipEvent_t ev0
         default: break;
     }
 #undef PULSE_SCORE_CASE
+}
+
+template <int DT>
+static void launch_average_dt(int G, hipStream_t st, const void* q, const void* digests, const int64_t* blk_off,
+                              int32_t B, int64_t total, int32_t Hq, int32_t H, int32_t n_sink, int32_t n_local,
+                              float* scores) {
+#define PULSE_AVERAGE_CASE(g)                                                                                  \
+    case g:                                                                                                    \
+        launch_average_t<DT, g>(st, q, digests, blk_off, B, total, Hq, H, n_sink, n_local, scores);            \
+        break;
+    switch (G) {
+        PULSE_AVERAGE_CASE(1) PULSE_AVERAGE_CASE(2) PULSE_AVERAGE_CASE(3) PULSE_AVERAGE_CASE(4)
+        PULSE_AVERAGE_CASE(5) PULSE_AVERAGE_CASE(6) PULSE_AVERAGE_CASE(7) PULSE_AVERAGE_CASE(8)
+        PULSE_AVERAGE_CASE(9) PULSE_AVERAGE_CASE(10) PULSE_AVERAGE_CASE(11) PULSE_AVERAGE_CASE(12)
+        PULSE_AVERAGE_CASE(13) PULSE_AVERAGE_CASE(14) PULSE_AVERAGE_CASE(15) PULSE_AVERAGE_CASE(16)
+        default: break;
+    }
+#undef PULSE_AVERAGE_CASE
+}
+
+// One head: its scores are the average.  Up to kScoreLargeBlocks digests one launch scores and
+// averages (8 heads x 256 blocks 15.9 -> 11.9 us with the selection, 2 heads x 8450 15.7 ->
+// 12.3); larger sets stream better with neighbouring workgroups on one head's digests, so every
+// head scores into ws first (8 heads x 65536 blocks: 43 us and 3 of averaging; in one launch
+// 47 to 60, whether groups took heads in turn or pairs of up to 8 blocks and 8 heads).
+hipError_t launch_average_scores(const pulse_shape& s, const void* q, const void* digests, const int64_t* blk_off,
+                                 int32_t B, int64_t total_blocks, int32_t n_sink, int32_t n_local, float* scores,
+                                 float* head_scores, hipStream_t st) {
+    if (s.num_kv_heads == 1)
+        return launch_score(s, q, digests, blk_off, B, total_blocks, 0, n_sink, n_local, scores, 1, st);
+    if (total_blocks * s.num_kv_heads > kScoreLargeBlocks) {
+        hipError_t e = launch_score(s, q, digests, blk_off, B, total_blocks, 0, n_sink, n_local, head_scores,
+                                    s.num_kv_heads, st);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(average_scores_kernel, dim3((unsigned)((total_blocks + 255) / 256)), dim3(256),
+                           (uint32_t)(sizeof(int64_t) * ((size_t)B + 1)), st, head_scores, blk_off, B, total_blocks,
+                           s.num_kv_heads, n_sink, n_local, scores);
+        return hipGetLastError();
+    }
+    if (total_blocks == 0) return hipSuccess;
+    const int32_t H = s.num_kv_heads, G = s.num_q_heads / H;
+    if (s.dtype == PULSE_BF16)
+        launch_average_dt<PULSE_BF16>(G, st, q, digests, blk_off, B, total_blocks, s.num_q_heads, H, n_sink, n_local,
+                                      scores);
+    else
+        launch_average_dt<PULSE_F16>(G, st, q, digests, blk_off, B, total_blocks, s.num_q_heads, H, n_sink, n_local,
+                                     scores);
+    return hipGetLastError();
 }
 
 hipError_t launch_score(const pulse_shape& s, const void* q, const void* digests, const int64_t* blk_off,

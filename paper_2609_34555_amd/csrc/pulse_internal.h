@@ -274,7 +274,10 @@ hipError_t launch_attention(const pulse_shape& s, const void* q, const void* poo
                             int32_t* status, hipStream_t st, hipEvent_t split_done = nullptr,
                             hipEvent_t done = nullptr, __bf16* x = nullptr);
 
-hipError_t launch_average_scores(const float* sc, int64_t total_blocks, int32_t H, float* avg, hipStream_t st);
+// Scores averaged over the KV heads; digests and head_scores (scratch) stacked along the heads.
+hipError_t launch_average_scores(const pulse_shape& s, const void* q, const void* digests, const int64_t* blk_off,
+                                 int32_t B, int64_t total_blocks, int32_t n_sink, int32_t n_local, float* scores,
+                                 float* head_scores, hipStream_t st);
 // Middle Attention Mass (variants.hip): the split of the context pass and its launch.
 struct MamPlan {
     int32_t entries_per_wave;  // blocks of one wave (at most 64)

@@ -1,11 +1,10 @@
 // variants.hip -- the selection strategies the paper compares SoloHead with,
 // and the Middle Attention Mass that picks the solo head (Sec. 4.4.1, Eq. 2).
 //
-// Average selection: every KV head scores the blocks with its own digests
-// (the score kernel over a head grid axis), the scores are averaged over the
-// heads, and one top-k on the average is shared by all heads.  Averaging the
-// per-KV-head scores (each already the mean over its G query heads) is the
-// mean over all query heads.
+// Average selection: every KV head scores the blocks with its own digests,
+// the scores are averaged over the heads (digest.hip), and one top-k on the
+// average is shared by all heads.  Averaging the per-KV-head scores (each
+// already the mean over its G query heads) is the mean over all query heads.
 //
 // MAM: for query head q, the softmax mass of its full attention that falls on
 // middle tokens is (sum of exp(logit) over the middle tokens) / (the same sum
@@ -17,26 +16,6 @@
 #include "pulse_internal.h"
 
 namespace pulse {
-
-// avg[b] = (1/H) * sum_h sc[h][b], heads summed in ascending order.
-__global__ __launch_bounds__(256) void average_scores_kernel(const float* __restrict__ sc, int64_t total_blocks,
-                                                             int32_t H, float* __restrict__ avg) {
-    const float inv = 1.f / (float)H;
-    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < total_blocks;
-         b += (int64_t)gridDim.x * blockDim.x) {
-        float s = 0.f;
-        for (int h = 0; h < H; ++h) s += sc[(size_t)h * total_blocks + b];
-        avg[b] = s * inv;
-    }
-}
-
-hipError_t launch_average_scores(const float* sc, int64_t total_blocks, int32_t H, float* avg, hipStream_t st) {
-    if (total_blocks == 0) return hipSuccess;
-    int64_t grid = (total_blocks + 255) / 256;
-    if (grid > 2048) grid = 2048;
-    hipLaunchKernelGGL(average_scores_kernel, dim3((unsigned)grid), dim3(256), 0, st, sc, total_blocks, H, avg);
-    return hipGetLastError();
-}
 
 constexpr int kMamWaves = 4;
 // Waves of a call: two per SIMD.  4 x 32K tokens took 58.0 / 59.1 / 58.1 us at 2048 / 4096 / 8192, one request

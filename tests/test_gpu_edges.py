@@ -159,3 +159,59 @@ def test_attention_split_plan(cnt, hq, hkv, bs, dt):
             # probabilities in two 16-bit parts (2^-16) and fp32 sums: 2^-14 of the values' size is well above both
             assert (out[r, h * G:(h + 1) * G] - torch.softmax(s, 1) @ V).abs().max() < 2.0 ** -14 * 5, (r, h)
             assert (lse[r, h * G:(h + 1) * G] - torch.logsumexp(s, 1)).abs().max() < 1e-5, (r, h)
+
+
+# Average scores: one head, head counts that divide a workgroup's 16 pairs and that do not, more than 16
+# heads, ragged and empty requests, and more digests than the one-launch limit (65536).
+AVG_EDGES = [([300, 0, 17], 8, 1, "bf16"), ([700, 31, 0, 0, 650], 6, 3, "f16"), ([900, 2000], 32, 8, "bf16"),
+             ([1, 16, 4000], 20, 5, "bf16"), ([500, 900], 34, 17, "f16"), ([131072, 7000], 32, 8, "bf16")]
+
+
+@pytest.mark.parametrize("ctx,hq,hkv,dt", AVG_EDGES)
+def test_average_scores_edges(ctx, hq, hkv, dt):
+    say(f"\n[gpu] average ctx={ctx} hq={hq} hkv={hkv}")
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(sum(ctx) + hq)
+    dtype = torch.bfloat16 if dt == "bf16" else torch.float16
+    B, G, bs, ns, nl = len(ctx), hq // hkv, 16, 1, 2
+    n = [-(-x // bs) for x in ctx]
+    off = [0]
+    for k in n:
+        off.append(off[-1] + k)
+    total = off[-1]
+    a = torch.randn((2, hkv, total, D), generator=gen, device=DEV, dtype=dtype)
+    dig = torch.stack([a.amin(0), a.amax(0)], 2).contiguous()  # [hkv][total][2][128]
+    q = torch.randn((B, hq, D), generator=gen, device=DEV, dtype=dtype)
+    blk_off = torch.tensor(off, dtype=torch.int64, device=DEV)
+    k_mid = torch.full((B,), 5, dtype=torch.int32, device=DEV)
+    sel = torch.full((B, 8), -7, dtype=torch.int32, device=DEV)
+    cnt = torch.zeros(B, dtype=torch.int32, device=DEV)
+    scores = torch.full((total,), 1e9, device=DEV)
+    st = torch.zeros(1, dtype=torch.int32, device=DEV)
+    sh = P.make_shape(hq, hkv, D, bs, P.PULSE_BF16 if dt == "bf16" else P.PULSE_F16)
+    nb = P.pulse_average_workspace_bytes(sh, B, 8, total)
+    ws = torch.full((nb,), 255, dtype=torch.uint8, device=DEV)
+    P.pulse_select_average(sh, q, dig, blk_off, B, total, k_mid, ns, nl, 8, sel, cnt, scores, st, ws, nb)
+    assert st.item() == 0
+    for r in range(B):
+        lo, hi = min(ns, n[r]), max(min(ns, n[r]), n[r] - nl)
+        b0 = off[r]
+        got = scores[b0:b0 + n[r]]
+        assert (got[:lo] == 1e9).all() and (got[hi:] == 1e9).all()  # forced blocks are left as they are
+        if hi <= lo:
+            continue
+        want = torch.zeros(hi - lo, dtype=torch.float64, device=DEV)
+        mass = torch.zeros_like(want)
+        for h in range(hkv):
+            mn, mx = dig[h, b0 + lo:b0 + hi, 0].double(), dig[h, b0 + lo:b0 + hi, 1].double()
+            for g in range(G):
+                qq = q[r, h * G + g].double()
+                want += mx @ qq.clamp(min=0) + mn @ qq.clamp(max=0)
+                mass += torch.maximum(mx.abs(), mn.abs()) @ qq.abs()
+        # fp32 sums of at most 128 G + Hkv terms: each within 2^-24 of a running sum no larger than the mass
+        err = (got[lo:hi].double() * G * hkv - want).abs() - 2.0 ** -24 * (128 * G / 16 + 8 + hkv) * mass
+        assert err.max().item() <= 0
+        k = min(5, hi - lo)
+        top = torch.sort(got[lo:hi], descending=True, stable=True).indices[:k] + lo
+        ids = torch.cat([torch.arange(lo, device=DEV), top, torch.arange(hi, n[r], device=DEV)]).sort().values
+        assert cnt[r].item() == len(ids) and torch.equal(sel[r, : len(ids)].long(), ids)
