@@ -103,6 +103,18 @@ __global__ __launch_bounds__(256) void build_digests_kernel(const uint16_t* __re
     }
 }
 
+// Sum of x over the 16 lanes of a group, in every lane: the additions of a butterfly (lane ^ 1,
+// ^ 2, ^ 4, ^ 8) as register permutes.  After the first two a quad's lanes are equal, so mirroring
+// the half row and the row brings the same values as exchanging with lane ^ 4 and lane ^ 8.
+__device__ inline float row_sum(float x) {
+    auto add = [&](int y) { x += __int_as_float(y); };
+    add(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, true));   // quad_perm [1, 0, 3, 2]
+    add(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, true));   // quad_perm [2, 3, 0, 1]
+    add(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x141, 0xF, 0xF, true));  // row_half_mirror
+    add(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x140, 0xF, 0xF, true));  // row_mirror
+    return x;
+}
+
 template <int DT>
 __device__ inline float dot2(uint32_t a, uint32_t b, float acc) {
     if constexpr (DT == PULSE_BF16)
@@ -222,8 +234,7 @@ __global__ __launch_bounds__(256) void score_kernel(const uint16_t* __restrict__
                 const uint32_t sel = (dmx[it][p] & qm) | (dmn[it][p] & ~qm);
                 acc = dot2<DT>(qp[g][p], sel, acc);
             }
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) acc += __shfl_xor(acc, off);
+        acc = row_sum(acc);
         if (sub == 0) scores[b] = acc / (float)G;
     }
 }
@@ -275,8 +286,7 @@ __global__ __launch_bounds__(256) void score_average_kernel(const uint16_t* __re
                 const uint32_t qm = ~(((qw & 0x80008000u) >> 15) * 0xFFFFu);
                 acc = dot2<DT>(qw, (dmx[c] & qm) | (dmn[c] & ~qm), acc);
             }
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) acc += __shfl_xor(acc, off);
+        acc = row_sum(acc);
         if (sub == 0) s_sc[p] = acc / (float)G;
     }
     __syncthreads();

@@ -66,12 +66,12 @@ __device__ inline RowScan row_scan(const uint32_t* row, int wid) {
 
 // LDS of one selecting workgroup.
 struct SelLds {
-    uint32_t hist[2][256];  // radix histograms: one counted while the other is cleared
+    __align__(16) uint32_t hist[2][256];  // radix histograms: one counted while the other is cleared
     uint32_t sh_prefix, sh_kk, sh_whole;
     uint32_t wc[kSelWaves][2];              // per-wave key min / max
     __align__(8) uint32_t eqc[kEntries];    // equal keys per (round, wave): the tie rule
     __align__(8) uint32_t cnt[kEntries];    // chosen (low 16 bits) | missing (high 16 bits) per (round, wave)
-    __align__(8) uint32_t rb[kEntries];     // missing-run starts in the wave (bits 0-7), first (8) / last (9) lane missing
+    __align__(8) uint32_t rb[kEntries];     // missing-run starts in the wave (round 0: bits 0-15), first (16) / last (17) lane missing
     int32_t sh_err;
 };
 
@@ -280,38 +280,49 @@ __device__ inline void select_request(SelLds& L, const float* rsc, const float (
         // Per (round, wave): chosen and missing counts and missing-run starts, as
         // bytes (round u in byte u & 3 of word u >> 2) summed over the wave by
         // DPP scans, which also give each lane its rank among the wave's chosen
-        // (missing) lanes of every round.
-        const uint32_t pm = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)miss_m, 0x138, 0xF, 0xF, false);  // wave_shr:1
-        const uint32_t st_m = miss_m & ~pm;  // missing, the block before (in this wave's round) not
-        uint32_t xs[kWords], xm[kWords];
-        const uint32_t m_first = (uint32_t)__builtin_amdgcn_readlane((int)miss_m, 0);
-        const uint32_t m_last = (uint32_t)__builtin_amdgcn_readlane((int)miss_m, 63);
+        // (missing) lanes of every round.  Without a table nothing is missing.
+        uint32_t xs[kWords], xm[kWords] = {};
 #pragma unroll
         for (int h = 0; h < kWords; ++h) {
-            const uint32_t bs = spread_bytes(sel_m >> (4 * h)), bm = spread_bytes(miss_m >> (4 * h));
-            const uint32_t is = wave_scan(bs, 0u, OpAdd()), im = wave_scan(bm, 0u, OpAdd());
+            const uint32_t bs = spread_bytes(sel_m >> (4 * h));
+            const uint32_t is = wave_scan(bs, 0u, OpAdd());
             xs[h] = is - bs;  // lanes below, per round
-            xm[h] = im - bm;
-            const uint32_t ts = last_lane(is), tm = last_lane(im);
-            const uint32_t tst = last_lane(wave_scan(spread_bytes(st_m >> (4 * h)), 0u, OpAdd()));
+            const uint32_t ts = last_lane(is);
+            uint32_t tm = 0;
+            if (plan) {
+                const uint32_t bm = spread_bytes(miss_m >> (4 * h));
+                const uint32_t im = wave_scan(bm, 0u, OpAdd());
+                xm[h] = im - bm;
+                tm = last_lane(im);
+            }
             if (lane >= 4 * h && lane < 4 * h + 4) {  // lane u writes this wave's entry of round u
                 const int sh = 8 * (lane & 3);
-                const int e = lane * kSelWaves + wid;
-                L.cnt[e] = ((ts >> sh) & 0xFFu) | (((tm >> sh) & 0xFFu) << 16);
-                L.rb[e] = ((tst >> sh) & 0xFFu) | (((m_first >> lane) & 1u) << 8) | (((m_last >> lane) & 1u) << 9);
+                L.cnt[lane * kSelWaves + wid] = ((ts >> sh) & 0xFFu) | (((tm >> sh) & 0xFFu) << 16);
             }
+        }
+        if (plan) {
+            const uint32_t pm =
+                (uint32_t)__builtin_amdgcn_update_dpp(0, (int)miss_m, 0x138, 0xF, 0xF, false);  // wave_shr:1
+            const uint32_t st_m = miss_m & ~pm;  // missing, the block before (in this wave's round) not
+            const uint32_t m_first = (uint32_t)__builtin_amdgcn_readlane((int)miss_m, 0);
+            const uint32_t m_last = (uint32_t)__builtin_amdgcn_readlane((int)miss_m, 63);
+            // the wave's starts of all rounds in its entry of round 0; first and last bits in every round's
+            const uint32_t starts = last_lane(wave_scan((uint32_t)__popc(st_m), 0u, OpAdd()));
+            if (lane < kRounds)
+                L.rb[lane * kSelWaves + wid] =
+                    (lane == 0 ? starts : 0u) | (((m_first >> lane) & 1u) << 16) | (((m_last >> lane) & 1u) << 17);
         }
         __syncthreads();
         const RowScan cs = row_scan(L.cnt, wid);
-        {
+        if (plan) {
             // runs: starts counted in each entry, less those that continue the previous
             // entry's last block (the previous tile's last block for entry 0)
             const u32x2 rr = *reinterpret_cast<const u32x2*>(&L.rb[2 * lane]);
-            const uint32_t l1 = (rr[1] >> 9) & 1u;
+            const uint32_t l1 = (rr[1] >> 17) & 1u;
             uint32_t pl = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)l1, 0x138, 0xF, 0xF, false);  // wave_shr:1
             if (lane == 0) pl = last_carry;
-            const uint32_t cont = (pl & (rr[0] >> 8) & 1u) + (((rr[0] >> 9) & 1u) & ((rr[1] >> 8) & 1u));
-            runs += last_lane(wave_scan((rr[0] & 0xFFu) + (rr[1] & 0xFFu) - cont, 0u, OpAdd()));
+            const uint32_t cont = (pl & (rr[0] >> 16) & 1u) + (((rr[0] >> 17) & 1u) & ((rr[1] >> 16) & 1u));
+            runs += last_lane(wave_scan((rr[0] & 0xFFFFu) + (rr[1] & 0xFFFFu) - cont, 0u, OpAdd()));
             last_carry = last_lane(l1);
         }
 #pragma unroll
@@ -346,6 +357,158 @@ __device__ inline void select_request(SelLds& L, const float* rsc, const float (
     }
 }
 
+// Requests of up to kSmallBlocks blocks: one wave, no barrier.  Lane l holds blocks l + 64 u, so
+// block order is (u, lane) and positions are counts of ballots.  The threshold comes from the same
+// radix select on the offsets key - min key, its histogram the wave's own.  One request of 256
+// blocks: 6.4 us on the general path, whose time there is barriers, 4.9 here (5.9 with a search
+// of the threshold bit by bit, by counts of ballots).
+// Arguments as for select_request; hist has 256 words, v and tpre hold blocks l + 64 u.
+constexpr int kSmallRounds = 8;
+constexpr int kSmallBlocks = kSmallRounds * kWave;
+
+// LDS accesses of a wave's lanes to one another's words are kept in program order (the hardware
+// executes a wave's LDS instructions in order).
+__device__ inline void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+__device__ inline uint32_t lanes_below(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+__device__ inline void select_small(uint32_t* hist, const float (&v)[kSmallRounds], const int32_t (&tpre)[kSmallRounds], int n,
+                                    int32_t k_mid_r, int32_t n_sink, int32_t n_local, int32_t k_max, int32_t* out,
+                                    bool plan, int32_t max_blocks, int32_t n_slots, int32_t* miss,
+                                    int32_t* sel_cnt_r, int32_t* miss_cnt_r, int32_t* run_cnt_r,
+                                    int32_t* req_err_r, int32_t* status) {
+    const int lane = threadIdx.x & 63;
+    const int64_t lo = n_sink, hi = (int64_t)n - n_local;  // middle blocks [lo, hi)
+    const int nc = hi > lo ? (int)(hi - lo) : 0;
+    const int k = k_mid_r < 0 ? 0 : (k_mid_r > nc ? nc : k_mid_r);
+    const int cnt = (n - nc) + k;
+    if (cnt > k_max) {
+        for (int i = lane; i < k_max; i += kWave) out[i] = -1;
+        if (lane == 0) {
+            report(status, PULSE_ERR_SELECT_OVERFLOW);
+            *sel_cnt_r = 0;
+            if (plan) { *miss_cnt_r = 0; *run_cnt_r = 0; *req_err_r = 0; }
+        }
+        return;
+    }
+    // offset of a middle block's key from the least one (0 for other blocks, which `mid` leaves out)
+    uint32_t off[kSmallRounds];
+    uint64_t mid[kSmallRounds];
+    uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
+#pragma unroll
+    for (int u = 0; u < kSmallRounds; ++u) {
+        const int j = lane + u * kWave;
+        const bool m = j < n && j >= lo && j < hi;
+        mid[u] = __ballot(m);
+        off[u] = key32(v[u]);
+        kmin = min(kmin, m ? off[u] : 0xFFFFFFFFu);
+        kmax = max(kmax, m ? off[u] : 0u);
+    }
+    // chosen: middle blocks whose masked offset is above T, and the first need_eq with T
+    uint32_t T = 0, T_mask = 0;
+    int need_eq = k;  // (k = 0 and k = nc: none and all of the equal ones)
+    if (k > 0 && k < nc) {
+        kmin = last_lane(wave_scan(kmin, 0xFFFFFFFFu, OpMin()));
+        kmax = last_lane(wave_scan(kmax, 0u, OpMax()));
+#pragma unroll
+        for (int u = 0; u < kSmallRounds; ++u) off[u] -= kmin;
+        const uint32_t span = kmax - kmin;
+        if (span) {
+            const int top = 31 - __clz(span);
+            uint32_t mask = top >= 31 ? 0u : ~((2u << top) - 1u);  // offset bits already decided
+            uint32_t prefix = 0u, kk = (uint32_t)k;
+            for (int shift = top - 7;; shift -= 8) {
+                const int sh = shift > 0 ? shift : 0;
+                const uint32_t dmask = shift >= 0 ? 255u : (255u >> -shift);
+                reinterpret_cast<u32x4*>(hist)[lane] = u32x4{0, 0, 0, 0};
+                wave_lds_order();
+#pragma unroll
+                for (int u = 0; u < kSmallRounds; ++u) {
+                    if (u * kWave >= n) break;  // wave-uniform
+                    if (((mid[u] >> lane) & 1u) && (off[u] & mask) == prefix)
+                        atomicAdd(&hist[(off[u] >> sh) & dmask], 1u);
+                }
+                wave_lds_order();
+                // lane owns digits 4 lane .. 4 lane + 3: the one with above(d) < kk <= above(d) + hist[d]
+                const u32x4 c = reinterpret_cast<const u32x4*>(hist)[lane];
+                wave_lds_order();
+                const uint32_t incl = wave_scan(c[0] + c[1] + c[2] + c[3], 0u, OpAdd());
+                uint32_t above = last_lane(incl) - incl, digit = 0, left = 0, whole = 0;
+                bool here = false;
+#pragma unroll
+                for (int i = 3; i >= 0; --i) {
+                    if (above < kk && kk <= above + c[i]) {
+                        here = true;
+                        digit = (uint32_t)(4 * lane + i);
+                        left = kk - above;
+                        whole = kk == above + c[i];
+                    }
+                    above += c[i];
+                }
+                const int at = __ffsll((unsigned long long)__ballot(here)) - 1;
+                prefix |= (uint32_t)__builtin_amdgcn_readlane((int)digit, at) << sh;
+                kk = (uint32_t)__builtin_amdgcn_readlane((int)left, at);
+                mask |= dmask << sh;
+                if (sh == 0 || __builtin_amdgcn_readlane((int)whole, at)) break;
+            }
+            T = prefix;
+            T_mask = mask;
+            need_eq = (int)kk;
+        }  // else all keys are equal: T_mask = 0, the first k are taken
+    }
+    int sel_carry = 0, miss_carry = 0, eq_carry = 0, runs = 0;
+    uint64_t prev = 0;  // whether the block before this round is missing
+    bool err = false;
+#pragma unroll
+    for (int u = 0; u < kSmallRounds; ++u) {
+        if (u * kWave >= n) break;  // wave-uniform
+        const int j = lane + u * kWave;
+        const bool m = (mid[u] >> lane) & 1u;
+        const uint32_t mo = off[u] & T_mask;
+        const uint64_t eq = __ballot(m && mo == T);
+        const bool take = m && (mo > T || (((eq >> lane) & 1u) && eq_carry + (int)lanes_below(eq) < need_eq));
+        eq_carry += __popcll(eq);
+        const bool sel = j < n && (!m || take);
+        const uint64_t sm = __ballot(sel);
+        if (sel) {
+            const int pos = sel_carry + (int)lanes_below(sm);
+            if (pos < k_max) out[pos] = j;
+        }
+        sel_carry += __popcll(sm);
+        if (plan) {
+            bool ms = false;
+            if (sel) {
+                if (j >= max_blocks || tpre[u] >= n_slots) err = true;
+                else ms = tpre[u] < 0;
+            }
+            const uint64_t mm = __ballot(ms);
+            if (ms) {
+                const int pos = miss_carry + (int)lanes_below(mm);
+                if (pos < k_max) miss[pos] = j;
+            }
+            miss_carry += __popcll(mm);
+            runs += __popcll(mm & ~((mm << 1) | prev));
+            prev = mm >> 63;
+        }
+    }
+    for (int i = cnt + lane; i < k_max; i += kWave) out[i] = -1;
+    const bool any_err = __ballot(err) != 0;
+    if (lane == 0) {
+        *sel_cnt_r = cnt;
+        if (plan) {
+            *miss_cnt_r = miss_carry;
+            *run_cnt_r = runs;
+            *req_err_r = any_err ? PULSE_ERR_BAD_INDEX : 0;
+            if (any_err) report(status, PULSE_ERR_BAD_INDEX);
+        }
+    }
+}
+
 // grid = (B, heads): blockIdx.x = request, blockIdx.y = selecting head slot
 // (always 0 for SoloHead; 0..Hkv-1 for headwise selection, whose per-head
 // scores, selections and plans are stacked along the head dimension).
@@ -372,31 +535,63 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
     // Loads issued before the request's extent is known, so that the common case
     // costs one memory round trip: the scores at the offsets the request has when
     // all requests are equally long (a wrong guess is reloaded once blk_off is
-    // known), then this thread's table entries of the first tile (blocks
-    // tid + 1024 u that exist in the row).  The scores come first: the key phase
-    // waits for them alone, and the table loads complete behind it.
+    // known), then the table entries of the first tile (blocks that exist in the
+    // row).  The scores come first: the key phase waits for them alone, and the
+    // table loads complete behind it.  Where equal requests would be small, the
+    // first wave loads in the small path's order.
     const int64_t n_eq = total_blocks / B;
     const int64_t b0_eq = (int64_t)r * n_eq;
-    const bool spec = n_eq >= 1 && n_eq <= kTile;
-    float sv[kRounds];
-    if (spec) {
+    const int32_t* trow = plan ? table + (size_t)r * max_blocks : nullptr;
+    const bool spec_small = n_eq >= 1 && n_eq <= kSmallBlocks;
+    const bool spec = n_eq > kSmallBlocks && n_eq <= kTile;
+    float ss[kSmallRounds], sv[kRounds];
+    int32_t ts[kSmallRounds], tpre[kRounds];
+    auto load_small = [&](const float* sc, int64_t n_sc) {
+        const int lane = tid & 63;
+#pragma unroll
+        for (int u = 0; u < kSmallRounds; ++u) {
+            const int j = lane + u * kWave;
+            ss[u] = u * kWave < n_sc ? sc[j < n_sc ? j : n_sc - 1] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kSmallRounds; ++u) {
+            const int j = lane + u * kWave;
+            ts[u] = (plan && u * kWave < n_sc && j < max_blocks) ? trow[j] : -1;
+        }
+    };
+    auto load_table = [&]() {
 #pragma unroll
         for (int u = 0; u < kRounds; ++u) {
-            if (u * kSelThreads >= n_eq) break;  // workgroup-uniform: no key of this slot exists
             const int j = tid + u * kSelThreads;
-            sv[u] = scores[b0_eq + (j < n_eq ? j : n_eq - 1)];
+            tpre[u] = (plan && j < max_blocks) ? trow[j] : -1;
         }
-    }
-    int32_t tpre[kRounds];
+    };
+    if (spec_small) {
+        if (tid < kWave) load_small(scores + b0_eq, n_eq);
+    } else {
+        if (spec) {
 #pragma unroll
-    for (int u = 0; u < kRounds; ++u) {
-        const int j = tid + u * kSelThreads;
-        tpre[u] = (plan && j < max_blocks) ? table[(size_t)r * max_blocks + j] : -1;
+            for (int u = 0; u < kRounds; ++u) {
+                if (u * kSelThreads >= n_eq) break;  // workgroup-uniform: no key of this slot exists
+                const int j = tid + u * kSelThreads;
+                sv[u] = scores[b0_eq + (j < n_eq ? j : n_eq - 1)];
+            }
+        }
+        load_table();
     }
     const int64_t b0 = blk_off[r];
     const int64_t n = blk_off[r + 1] - b0;
     const float* rsc = scores + b0;  // this request's scores, by block
     if (plan && free_head && r == 0 && hy == 0 && tid == 0) misc[0] = *free_head;
+    if (n <= kSmallBlocks) {
+        if (tid >= kWave) return;
+        if (!spec_small || b0 != b0_eq || n != n_eq) load_small(rsc, n);
+        select_small(L.hist[0], ss, ts, (int)n, k_mid[r], n_sink, n_local, k_max, sel_idx + (size_t)r * k_max, plan, max_blocks,
+                     n_slots, plan ? miss_list + (size_t)r * k_max : nullptr, sel_cnt + r, miss_cnt + r, run_cnt + r,
+                     req_err + r, status);
+        return;
+    }
+    if (spec_small) load_table();
     float v[kRounds];
     if (n <= kTile) {
         const bool hit = spec && b0 == b0_eq && n == n_eq;
@@ -408,7 +603,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(
         }
     }
     select_request(L, rsc, v, tpre, n, k_mid[r], n_sink, n_local, k_max, sel_idx + (size_t)r * k_max,
-                   plan ? table + (size_t)r * max_blocks : nullptr, max_blocks, n_slots,
+                   trow, max_blocks, n_slots,
                    plan ? miss_list + (size_t)r * k_max : nullptr, sel_cnt + r, miss_cnt + r, run_cnt + r,
                    req_err + r, status);
 }

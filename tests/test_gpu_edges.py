@@ -215,3 +215,43 @@ def test_average_scores_edges(ctx, hq, hkv, dt):
         top = torch.sort(got[lo:hi], descending=True, stable=True).indices[:k] + lo
         ids = torch.cat([torch.arange(lo, device=DEV), top, torch.arange(hi, n[r], device=DEV)]).sort().values
         assert cnt[r].item() == len(ids) and torch.equal(sel[r, : len(ids)].long(), ids)
+
+
+# Block counts around the one-wave selection (up to 512 blocks), its 64-block rounds and the general path, with
+# every budget from none to all and blocks that are copies of one another (ties go to the lowest index).
+@pytest.mark.parametrize("n", [[1, 2, 63, 64], [65, 127, 128, 0], [511, 512, 513, 3], [512] * 3, [200] * 4, [700, 40]])
+@pytest.mark.parametrize("copies", [0, 1])
+def test_select_block_counts(n, copies):
+    say(f"\n[gpu] select n={n} copies={copies}")
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(sum(n) + copies)
+    B, total, ns, nl, G = len(n), sum(n), 1, 2, 4
+    off = [0]
+    for k in n:
+        off.append(off[-1] + k)
+    a = torch.randn((2, total, D), generator=gen, device=DEV, dtype=torch.bfloat16)
+    if copies:  # few distinct blocks
+        a = a[:, torch.randint(0, max(1, total // 16), (total,), generator=gen, device=DEV)]
+    dig = torch.stack([a.amin(0), a.amax(0)], 1).contiguous()
+    q = torch.randn((B, G, D), generator=gen, device=DEV, dtype=torch.bfloat16)
+    blk_off = torch.tensor(off, dtype=torch.int64, device=DEV)
+    sh = P.make_shape(G, 1, D, 16, P.PULSE_BF16)
+    k_max = max(n)
+    st = torch.zeros(1, dtype=torch.int32, device=DEV)
+    nb = P.pulse_workspace_bytes(sh, B, k_max, total)
+    ws = torch.zeros(nb, dtype=torch.uint8, device=DEV)
+    for share in (0.0, 0.02, 0.3, 0.97, 1.0):
+        k_mid = torch.tensor([int(share * x) for x in n], dtype=torch.int32, device=DEV)
+        sel = torch.full((B, k_max), -7, dtype=torch.int32, device=DEV)
+        cnt = torch.full((B,), -7, dtype=torch.int32, device=DEV)
+        scores = torch.zeros(total, device=DEV)
+        P.pulse_select_solohead(sh, q, dig, blk_off, B, total, 0, k_mid, ns, nl, k_max, sel, cnt, scores, st, ws, nb)
+        assert st.item() == 0
+        for r in range(B):
+            lo, hi = min(ns, n[r]), max(min(ns, n[r]), n[r] - nl)
+            k = min(int(share * n[r]), hi - lo)
+            s = scores[off[r] + lo: off[r] + hi]
+            top = torch.sort(s, descending=True, stable=True).indices[:k] + lo
+            ids = torch.cat([torch.arange(lo, device=DEV), top, torch.arange(hi, n[r], device=DEV)]).sort().values
+            assert cnt[r].item() == len(ids), (share, r)
+            assert torch.equal(sel[r, : len(ids)].long(), ids) and (sel[r, len(ids):] == -1).all(), (share, r)
