@@ -64,7 +64,7 @@ struct SplitArgs {
 // workgroups: at 16 requests x 65K tokens with budgets of 317 to 8192 tokens (lognormal
 // around 2048) 58.2 us before, 42.6 with it (188 MB; the split kernel at 5.7 TB/s).  Equal counts
 // keep the host's own split: 8 x 2048 tokens 16.2 us (16.7 with splits numbered before heads, as
-// before), 4 x 8192 at G 8 30.1 (30.4).
+// before), 4 x 8192 at G 8 30.2 (30.4); both HBM-bound between their first key and last value.
 constexpr int kPlanRequests = 64;
 
 struct Piece {
@@ -110,6 +110,24 @@ __device__ inline Piece plan_piece(int pr, int32_t raw, int32_t B, int32_t k_max
     p.cnt = __builtin_amdgcn_readlane(c, at);
     p.wg = pr - p.base;
     return p;
+}
+
+// 2^x as the hardware has it (1 ulp; results below 2^-126 are 0, far below what a sum of
+// probabilities with a largest one of 1 holds).
+__device__ inline float exp2_fast(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// Combination of the four 16-lane groups' values, in every lane: rows and halves are exchanged
+// between two copies in registers (v_permlane16_swap, v_permlane32_swap), no LDS round trip.
+// With this, exp2_fast and the accumulators rescaled only when a maximum moved: 8 x 2048 tokens
+// 16.2 -> 15.9 us, 4 x 8192 at G 8 30.2 -> 29.9, one request of 400 tokens 8.3 -> 7.8 in the kernel.
+template <typename Op>
+__device__ inline float across_groups(float x, Op op) {
+    const uint32_t u = __float_as_uint(x);
+    const u32x2 a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const float y = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const uint32_t w = __float_as_uint(y);
+    const u32x2 b = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+    return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
 // Attention of one wave over entries [e0, e0 + ne) of request r, KV head h;
@@ -185,12 +203,14 @@ __device__ inline void attend_split(const uint16_t* __restrict__ q, const uint16
     };
 
     // One 32-token step at a time: K is loaded first, V once the S tile is issued, so
-    // the V loads overlap the softmax and fewer operands are live (143 VGPRs, 3 waves
+    // the V loads overlap the softmax and fewer operands are live (125 VGPRs, 4 waves
     // per SIMD).  The other resident waves hide the load latency.  Measured slower:
     // loading K and V together (154 VGPRs; 2-5%), prefetching the next step into
     // registers as well (223 VGPRs; another 1-2%), and, for splits of two steps,
     // issuing all four loads before the first product (177 VGPRs; 11% slower on
-    // 8 requests x 2048 selected tokens).
+    // 8 requests x 2048 selected tokens; no faster on one request either), and keys
+    // loaded with neighbouring lanes on neighbouring pieces and staged through LDS,
+    // pipelined by a step (2-4% slower on 8 x 2048, equal on larger calls).
 #pragma unroll 1
     for (int t0 = 0; t0 < tokens; t0 += kChunkTokens) {
         vec ka[2][4], vb[8];
@@ -222,16 +242,15 @@ __device__ inline void attend_split(const uint16_t* __restrict__ q, const uint16
             if (!pv_ok || pv_row + i >= pv_nv) x[i] = -INFINITY;
             cm = fmaxf(cm, x[i]);
         }
-        cm = fmaxf(cm, __shfl_xor(cm, 16));
-        cm = fmaxf(cm, __shfl_xor(cm, 32));
+        cm = across_groups(cm, [](float a, float b) { return fmaxf(a, b); });
         const float m_new = fmaxf(m_run, cm);
         const float m_use = m_new == -INFINITY ? 0.f : m_new;
-        const float alpha = exp2f(m_run - m_use);
+        const float alpha = exp2_fast(m_run - m_use);
         float psum = 0.f;
         vec ph, pl;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const float p = exp2f(x[i] - m_use);
+            const float p = exp2_fast(x[i] - m_use);
             psum += p;
             typename M::elem hi, lo;
             M::split(p, hi, lo);
@@ -240,12 +259,15 @@ __device__ inline void attend_split(const uint16_t* __restrict__ q, const uint16
         }
         l_run = l_run * alpha + psum;
         m_run = m_new;
-        // rescale accumulator rows g' = 4*grp + v by alpha of query g'
+        // rescale accumulator rows g' = 4*grp + v by alpha of query g' (not while they are zero,
+        // and not when no query's maximum moved)
+        if (t0 > 0 && __ballot(alpha != 1.f)) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const float av = __shfl(alpha, 4 * grp + v);
+            for (int v = 0; v < 4; ++v) {
+                const float av = __shfl(alpha, 4 * grp + v);
 #pragma unroll
-            for (int t = 0; t < 8; ++t) acc[t][v] *= av;
+                for (int t = 0; t < 8; ++t) acc[t][v] *= av;
+            }
         }
         // --- O += P . V  (hi and lo parts of P)
 #pragma unroll
@@ -254,11 +276,10 @@ __device__ inline void attend_split(const uint16_t* __restrict__ q, const uint16
             acc[t] = M::mac(pl, vb[t], acc[t]);
         }
     }
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
+    l_run = across_groups(l_run, [](float a, float b) { return a + b; });
 }
 
-// grid = (n_wg0 * Hkv, B), numbered in a row: workgroup p is piece p / Hkv of KV head p % Hkv (see the split plan); wave w of a
+// grid = (Hkv, n_wg0, B): in this order workgroup p is piece p / Hkv of KV head p % Hkv (see the split plan); wave w of a
 // request's workgroup wg owns split W * wg + w of eps entries.  Dynamic LDS: O [W][G][128] floats then
 // (m, l) [W][G] float2.
 template <int DT, int BS, int W>
@@ -275,14 +296,13 @@ __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
     float2* s_ml = reinterpret_cast<float2*>(smem + W * G * kHeadDim);  // [W][G]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, grp = lane >> 4;
-    const uint32_t id = blockIdx.y * gridDim.x + blockIdx.x;
-    const int pr = (int)(id / (uint32_t)Hkv), h = (int)(id % (uint32_t)Hkv);
+    const int h = blockIdx.x, pr = (int)(blockIdx.z * gridDim.y + blockIdx.y);
 
     // this wave's selected blocks (one per lane) are loaded with the counts they depend on, at the place
     // they have when all counts are equal: one memory round trip fewer before the first K load
     Piece p;
-    p.r = pr / sp.n_wg;
-    p.wg = pr % sp.n_wg;
+    p.r = blockIdx.z;
+    p.wg = blockIdx.y;
     p.eps = sp.eps;
     const bool planned = sp.planned;
     auto load_j = [&]() {
@@ -292,7 +312,7 @@ __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
     int32_t j_lane = load_j();
     if (planned) {
         const int32_t raw = lane < B ? sel_cnt[lane] : 0;
-        if (id == 0 && wave == 0 && (raw < 0 || raw > k_max)) report(status, PULSE_ERR_BAD_INDEX);
+        if (pr == 0 && h == 0 && wave == 0 && (raw < 0 || raw > k_max)) report(status, PULSE_ERR_BAD_INDEX);
         p.cnt = k_max;
         p.nwg = sp.n_wg;
         if (!equal_counts(raw, B, k_max, lane)) {
@@ -340,7 +360,7 @@ __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
     }
     __syncthreads();
     // merge the W waves: thread handles outputs (g, c) = (idx / 128, idx % 128)
-    const size_t unit = id;
+    const size_t unit = (size_t)pr * Hkv + h;
     for (int idx = tid; idx < G * kHeadDim; idx += kThreads) {
         const int g = idx / kHeadDim, c = idx % kHeadDim;
         float Mx = -INFINITY;
@@ -351,7 +371,7 @@ __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
 #pragma unroll
             for (int w = 0; w < W; ++w) {
                 const float2 ml = s_ml[w * G + g];
-                const float wt = ml.x == -INFINITY ? 0.f : exp2f(ml.x - Mx);
+                const float wt = ml.x == -INFINITY ? 0.f : exp2_fast(ml.x - Mx);
                 L += ml.y * wt;
                 a += s_o[(w * G + g) * kHeadDim + c] * wt;
             }
@@ -490,7 +510,7 @@ hipError_t launch_attention(const pulse_shape& s, const void* q, const void* poo
     const AttnPlan p = attn_plan(B, Hkv, k_max, s.block_size);
     const int W = attn_waves(G);
     const int32_t n_wg = (p.n_split + W - 1) / W;
-    const dim3 grid((unsigned)n_wg * (unsigned)Hkv, (unsigned)B);  // numbered in a row
+    const dim3 grid((unsigned)Hkv, (unsigned)n_wg, (unsigned)B);
     SplitArgs sp;
     sp.eps = p.entries_per_split;
     sp.n_wg = n_wg;
