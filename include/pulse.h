@@ -552,6 +552,8 @@ PULSE_API pulse_status pulse_irq_destroy(pulse_irq* irq);
  * through the gather-scatter engine instead, submitted on the compute stream, and its
  * host-side completion is the flag; the gather kernel path stalls concurrent
  * kernels on MI355X while it reads host memory, the engine's DMA does not.
+ * BLOCKING without an engine runs everything in the compute stream's order,
+ * after the work that was on the I/O stream when the step began.
  * Results of the offload batch are those of pulse_decode_layer on each layer
  * (mean_resume_us / mean_recall_us are -1 with an engine).
  * overlap_depth (optional host int32 [n_offload_layers]) receives the normal

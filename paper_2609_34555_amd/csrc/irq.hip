@@ -29,7 +29,8 @@
 //              queued), checking the flag between enqueues;
 //   BLOCKING   no interleaving: each offload layer waits for its recall with
 //              no other work, then one normal layer runs (a single-batch
-//              schedule, the baseline).
+//              schedule, the baseline).  With the gather kernel everything is
+//              in one stream, and the host does not look at the flag.
 //
 // A normal-batch layer is decode attention over its resident KV (every
 // block selected; the attention kernel of this library) followed by a SwiGLU
@@ -309,8 +310,8 @@ static pulse_status check_normal(const pulse_normal_layer* n) {
     return PULSE_OK;
 }
 
-// Enqueue one normal-batch layer on irq->cmp; ev_attn is recorded after its
-// attention, ev_end after its FFN.
+// Enqueue one normal-batch layer on irq->cmp; ev_attn (optional) is recorded after its
+// attention, ev_end (optional) after its FFN.
 static pulse_status normal_layer(pulse_irq* irq, const pulse_normal_layer& n, hipEvent_t ev_attn, hipEvent_t ev_end) {
     const hipStream_t hs = irq->cmp;
     const WsLayout w = ws_layout(n.shape, n.B, n.k_max, 0);
@@ -318,13 +319,13 @@ static pulse_status normal_layer(pulse_irq* irq, const pulse_normal_layer& n, hi
                          n.k_max, n.ctx_len, n.B, n.sm_scale, n.out, n.lse, ws_at<float>(n.ws, w.attn_o),
                          ws_at<float2>(n.ws, w.attn_ml), n.dev_status, hs, nullptr, nullptr, (__bf16*)n.x) != hipSuccess)
         return PULSE_ERR_HIP;
-    if (hipEventRecord(ev_attn, hs) != hipSuccess) return PULSE_ERR_HIP;
+    if (ev_attn && hipEventRecord(ev_attn, hs) != hipSuccess) return PULSE_ERR_HIP;
     const int32_t D = n.shape.num_q_heads * n.shape.head_dim, F = n.d_ff, B = n.B;
     // gu [B][2F] = x [B][D] . W_gu^T, h [B][F] = silu(g) * u
     if (launch_ffn_gemm<true>(n.x, n.w_gate_up, n.gu, n.h, B, F, D, hs) != hipSuccess) return PULSE_ERR_HIP;
     // y [B][D] = h [B][F] . W_down^T
     if (launch_ffn_gemm<false>(n.h, n.w_down, n.y, nullptr, B, D, F, hs) != hipSuccess) return PULSE_ERR_HIP;
-    if (hipEventRecord(ev_end, hs) != hipSuccess) return PULSE_ERR_HIP;
+    if (ev_end && hipEventRecord(ev_end, hs) != hipSuccess) return PULSE_ERR_HIP;
     return PULSE_OK;
 }
 
@@ -392,8 +393,12 @@ pulse_status pulse_irq_step(pulse_irq* irq, const pulse_layer_args* offload, int
     int64_t engine_pending = 0;  // engine call submitted and not yet seen complete
 
     auto run_normal = [&](bool wait_attn, bool wait_all) -> pulse_status {
-        hipEvent_t ea = irq->event(), ee = irq->event();
-        if (!ea || !ee) return PULSE_ERR_HIP;
+        hipEvent_t ea = nullptr, ee = nullptr;
+        if (mode != PULSE_IRQ_BLOCKING) {  // the modes that wait for layers
+            ea = irq->event();
+            ee = irq->event();
+            if (!ea || !ee) return PULSE_ERR_HIP;
+        }
         if (mode == PULSE_IRQ_ASYNC) {
             if ((int64_t)(ring.size() - ring_head) >= async_ahead) {
                 if (hipEventSynchronize(ring[ring_head]) != hipSuccess) return PULSE_ERR_HIP;
@@ -409,6 +414,23 @@ pulse_status pulse_irq_step(pulse_irq* irq, const pulse_layer_args* offload, int
         return PULSE_OK;
     };
 
+    // BLOCKING with the gather kernel: nothing runs beside a recall, so it goes from every XCD and
+    // on the compute stream, whose order is the wait.  (Through the I/O stream, the flag and the
+    // host the chip idled about 30 us per layer: two cross-stream waits, and the launches that
+    // followed the flag; 4 layers of a light offload batch beside 32 x 4K requests 1026 -> 901 us.)
+    // Work the caller left on the I/O stream still comes first.
+    const bool in_order = mode == PULSE_IRQ_BLOCKING && !engine;
+    if (in_order) {
+        const hipError_t q = hipStreamQuery(irq->io);
+        if (q == hipErrorNotReady) {
+            (void)hipGetLastError();  // an answer, not an error of a later call
+            hipEvent_t e = irq->event();
+            if (!e || hipEventRecord(e, irq->io) != hipSuccess || hipStreamWaitEvent(irq->cmp, e, 0) != hipSuccess)
+                result = PULSE_ERR_HIP;
+        } else if (q != hipSuccess) {
+            result = PULSE_ERR_HIP;
+        }
+    }
     for (size_t m = 0; m < L && result == PULSE_OK; ++m) {
         const pulse_layer_args& a = offload[m];
         ev_sel[m] = irq->event();
@@ -423,7 +445,12 @@ pulse_status pulse_irq_step(pulse_irq* irq, const pulse_layer_args* offload, int
             break;
         }
         int64_t seq = 0;
-        if (engine) {
+        if (in_order) {
+            if (layer_recall(a, irq->cmp, 8, ev_rc0[m], ev_rc1[m]) != hipSuccess) {
+                result = PULSE_ERR_HIP;
+                break;
+            }
+        } else if (engine) {
             result = pulse_gs_recall_submit(engine, a.host_kv, a.blk_off, a.B, a.sel_idx, a.sel_cnt, a.k_max,
                                             a.block_table, a.max_blocks, a.free_slots, a.free_head, a.n_free,
                                             a.slot_pool, a.n_slots, a.stats, a.dev_status, a.ws, a.ws_bytes, &seq,
@@ -455,7 +482,7 @@ pulse_status pulse_irq_step(pulse_irq* irq, const pulse_layer_args* offload, int
         // wait for the recall: normal layers run meanwhile, checked at layer boundaries
         int32_t depth = 0;
         const auto w0 = std::chrono::steady_clock::now();
-        while (!recall_done()) {
+        while (!in_order && !recall_done()) {
             if (std::chrono::duration<double>(std::chrono::steady_clock::now() - w0).count() > wait_limit_s) {
                 result = PULSE_ERR_TIMEOUT;
                 break;
@@ -469,7 +496,7 @@ pulse_status pulse_irq_step(pulse_irq* irq, const pulse_layer_args* offload, int
         depths[m] = depth;
         // resume the offload batch: its attention for layer m
         // (the engine marks a call complete only after its streams have drained)
-        if ((!engine && hipStreamWaitEvent(irq->cmp, ev_rc1[m], 0) != hipSuccess) ||
+        if ((!engine && !in_order && hipStreamWaitEvent(irq->cmp, ev_rc1[m], 0) != hipSuccess) ||
             hipEventRecord(ev_att[m], irq->cmp) != hipSuccess || layer_attention(a, irq->cmp) != hipSuccess) {
             result = PULSE_ERR_HIP;
             break;

@@ -255,3 +255,34 @@ def test_select_block_counts(n, copies):
             ids = torch.cat([torch.arange(lo, device=DEV), top, torch.arange(hi, n[r], device=DEV)]).sort().values
             assert cnt[r].item() == len(ids), (share, r)
             assert torch.equal(sel[r, : len(ids)].long(), ids) and (sel[r, len(ids):] == -1).all(), (share, r)
+
+
+def test_irq_blocking_step_follows_io_stream_work():
+    """The blocking step's recalls read what the I/O stream's earlier work wrote to the host store."""
+    from paper_2609_34555_amd import workloads as W
+    from parity import build
+    import numpy as np
+
+    say("\n[gpu] blocking step behind I/O stream work")
+    spec, seed = W.custom("behind", [640], Hq=4, Hkv=2, bs=16, k_mid=6)
+    w, st = build(spec, seed)
+    st.reset()
+    cmp_, io = torch.cuda.Stream(), torch.cuda.Stream()
+    sched = P.IrqScheduler(cmp_, io)
+    host = torch.from_numpy(w.kv.view(np.int16))
+    new = torch.full_like(host, 0x3C00, device=DEV)  # every key and value the same
+    a = torch.randn((4096, 4096), device=DEV)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(io):
+        for _ in range(20):  # some milliseconds of work ahead of the store's update
+            a = (a @ a).clamp(-1, 1)
+        host.copy_(new, non_blocking=True)
+    assert not io.query()
+    sched.step([st.layer_args()], [], mode="blocking")
+    torch.cuda.synchronize()
+    assert st.status() == 0 and st.recall_stats()[0] > 0
+    table = st.table_np()[0]
+    slots = [int(table[j]) for j in range(w.max_blocks) if table[j] >= 0 and w.table0[0, j] < 0]
+    assert len(slots) == st.recall_stats()[0]
+    assert (st.pool_np()[slots] == 0x3C00).all()
+    sched.destroy()
