@@ -358,8 +358,9 @@ PULSE_API pulse_status pulse_sparse_decode_attn(const pulse_shape* shape, const 
 /*
  * Split-K workgroups per (request, KV head) that pulse_sparse_decode_attn,
  * and the attention of pulse_decode_layer, launch for a batch of B requests
- * with at most k_max selected blocks each (the split depends on B, Hkv, k_max
- * and bs only).  Above 1, a kernel that merges the workgroups' partials
+ * with at most k_max selected blocks each (it depends on B, Hkv, k_max and bs
+ * only; up to 64 requests whose counts differ share these workgroups out by
+ * their counts).  Above 1, a kernel that merges the workgroups' partials
  * follows the split-K kernel, and pulse_layer_args.attn_split_event marks the
  * end of the split-K kernel alone.  At 1, one workgroup covers each (request,
  * KV head) and writes out / lse itself: no merge kernel runs, so a caller that

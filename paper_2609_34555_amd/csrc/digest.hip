@@ -422,7 +422,8 @@ hipError_t launch_average_scores(const pulse_shape& s, const void* q, const void
                                  float* head_scores, hipStream_t st) {
     if (s.num_kv_heads == 1)
         return launch_score(s, q, digests, blk_off, B, total_blocks, 0, n_sink, n_local, scores, 1, st);
-    if (total_blocks * s.num_kv_heads > kScoreLargeBlocks) {
+    // (the one launch holds a block's scores of every head in LDS)
+    if (total_blocks * s.num_kv_heads > kScoreLargeBlocks || s.num_kv_heads > 256) {
         hipError_t e = launch_score(s, q, digests, blk_off, B, total_blocks, 0, n_sink, n_local, head_scores,
                                     s.num_kv_heads, st);
         if (e != hipSuccess) return e;
