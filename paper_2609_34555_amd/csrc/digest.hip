@@ -303,8 +303,8 @@ __global__ __launch_bounds__(256) void score_average_kernel(const uint16_t* __re
 }
 
 // avg[b] = (1/H) * sum_h sc[h][b], heads summed in ascending order, eight of them in flight
-// at a time (one after the other: 4.8 us on 8 x 65536 scores).  Entries that were not scored
-// (forced blocks) are not written.
+// at a time (with them one after the other the whole call on 16 x 64K tokens, 8 heads, took
+// 53.4 us instead of 52.4).  Entries that were not scored (forced blocks) are not written.
 __global__ __launch_bounds__(256) void average_scores_kernel(const float* __restrict__ sc,
                                                              const int64_t* __restrict__ blk_off, int32_t B,
                                                              int64_t total_blocks, int32_t H, int32_t n_sink,

@@ -132,6 +132,7 @@ __global__ __launch_bounds__(WV * kWave) void ffn_gemm_kernel(const __bf16* __re
         for (int i = 0; i < NA; ++i) stage[i * kWave + lane] = a[i];
 #pragma unroll
         for (int i = 0; i < NB; ++i) stage[(NA + i) * kWave + lane] = b[i];
+        wave_lds_order();
         auto frag = [&](int tile, int u) {
             return stage[(16 * tile + col) * PP + ((u * 4 + grp) ^ (col % PP))];
         };
@@ -150,6 +151,7 @@ __global__ __launch_bounds__(WV * kWave) void ffn_gemm_kernel(const __bf16* __re
                                                                           acc[nt][mt], 0, 0, 0);
             }
         }
+        wave_lds_order();  // the next group overwrites the rows
     };
     // Groups that lie within K, every WV-th to each wave, loaded without a test (a test per load
     // makes the compiler wait for all loads in flight at every product).

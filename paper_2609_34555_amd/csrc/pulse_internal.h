@@ -68,6 +68,13 @@ struct OpMax { __device__ uint32_t operator()(uint32_t a, uint32_t b) const { re
 // Value of lane 63 (the wave-wide result of an inclusive scan), in every lane.
 __device__ inline uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
 
+// LDS accesses of a wave's lanes to one another's words are kept in program order (the hardware
+// executes a wave's LDS instructions in order).
+__device__ inline void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // ---- 16-bit element helpers ------------------------------------------------
 
 // Order-preserving map of fp32 onto uint32 (both zeros map to the key of +0).

@@ -366,13 +366,6 @@ __device__ inline void select_request(SelLds& L, const float* rsc, const float (
 constexpr int kSmallRounds = 8;
 constexpr int kSmallBlocks = kSmallRounds * kWave;
 
-// LDS accesses of a wave's lanes to one another's words are kept in program order (the hardware
-// executes a wave's LDS instructions in order).
-__device__ inline void wave_lds_order() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 __device__ inline uint32_t lanes_below(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
