@@ -37,7 +37,8 @@ struct MamSum {
     __device__ void merge_lanes(int off) {
         merge(__shfl_xor(m, off), __shfl_xor(all, off), __shfl_xor(mid, off));
     }
-    __device__ float mass() const { return all > 0.f ? mid / all : 0.f; }
+    // 0 where nothing was summed; a NaN among the logits reaches the mass
+    __device__ float mass() const { return all == 0.f ? 0.f : mid / all; }
 };
 
 // Mean of the G heads' masses, summed in ascending order; lane g holds head g's.
