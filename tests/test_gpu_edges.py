@@ -71,6 +71,26 @@ def test_mam_edges(ctx, hq, hkv, bs, dt, ns, nl):
     assert err < 1e-5
 
 
+@pytest.mark.parametrize("ctx", [100, 4096])  # one workgroup per head, several
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_mam_of_non_finite_keys_is_nan(ctx, bad):
+    """A key that makes a logit NaN or infinite makes its head's mass NaN, in no other head."""
+    say(f"\n[gpu] mam non-finite ctx={ctx} {bad}")
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(ctx)
+    pool, table, ctx_len, n, mb = _paged([ctx, ctx], 2, 16, torch.bfloat16, gen)
+    q = torch.rand((2, 8, D), generator=gen, device=DEV).add(0.5).bfloat16()
+    pool[table[1, 3].long(), 0, 1, 5 * D:6 * D] = bad  # request 1, head 1, token 5 of block 3
+    sh = P.make_shape(8, 2, D, 16, P.PULSE_BF16)
+    out = torch.zeros((2, 2), device=DEV)
+    st = torch.zeros(1, dtype=torch.int32, device=DEV)
+    nb = P.pulse_mam_workspace_bytes(sh, 2, mb)
+    ws = torch.zeros(nb, dtype=torch.uint8, device=DEV)
+    P.pulse_mam(sh, q, pool, pool.shape[0], table, mb, ctx_len, 2, 1, 2, D ** -0.5, out, st, ws, nb)
+    assert st.item() == 0
+    assert out.isnan().cpu().tolist() == [[False, False], [False, True]]
+
+
 # Rows of the FFN products per tile count (16, 32, 64 and beyond), hidden sizes below one group of
 # K steps, with a last step of 8 elements, and on either side of the two-tile rule (512 column tiles).
 FFN_CASES = [(1, 8, 2, 1, 100), (16, 24, 4, 2, 33), (17, 136, 8, 8, 16), (32, 1000, 4, 4, 300), (33, 512, 6, 3, 20),
@@ -163,6 +183,19 @@ def test_attention_split_plan(cnt, hq, hkv, bs, dt):
 
 # Average scores: one head, head counts that divide a workgroup's 16 pairs and that do not, more than 16
 # heads, ragged and empty requests, and more digests than the one-launch limit (65536).
+@pytest.mark.parametrize("hkv", [1, 8, 257])
+def test_average_of_no_blocks(hkv):
+    """Requests without blocks select nothing, whatever the head count."""
+    say(f"\n[gpu] average of no blocks hkv={hkv}")
+    i32 = dict(dtype=torch.int32, device=DEV)
+    sel, cnt, st = torch.full((2, 4), -7, **i32), torch.full((2,), 9, **i32), torch.zeros(1, **i32)
+    pad = torch.zeros((2, hkv, D), dtype=torch.bfloat16, device=DEV)
+    sh = P.make_shape(hkv, hkv, D, 16, P.PULSE_BF16)
+    P.pulse_select_average(sh, pad, pad, torch.zeros(3, dtype=torch.int64, device=DEV), 2, 0, torch.ones(2, **i32), 1, 1,
+                           4, sel, cnt, None, st, torch.zeros(256, dtype=torch.uint8, device=DEV), 256)
+    assert st.item() == 0 and (cnt == 0).all() and (sel == -1).all()
+
+
 AVG_EDGES = [([300, 0, 17], 8, 1, "bf16"), ([700, 31, 0, 0, 650], 6, 3, "f16"), ([900, 2000], 32, 8, "bf16"),
              ([1, 16, 4000], 20, 5, "bf16"), ([500, 900], 34, 17, "f16"), ([131072, 7000], 32, 8, "bf16")]
 
