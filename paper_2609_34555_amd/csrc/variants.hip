@@ -28,7 +28,12 @@ struct MamSum {
     float m = -INFINITY, all = 0.f, mid = 0.f;  // running max (log2 domain), sums of exp2(x - m)
     __device__ void merge(float m2, float all2, float mid2) {
         const float mn = fmaxf(m, m2);
-        if (mn == -INFINITY) return;
+        // without a maximum on either side the sums are 0, or NaN where every logit is (a maximum skips NaN)
+        if (mn == -INFINITY) {
+            all += all2;
+            mid += mid2;
+            return;
+        }
         const float a = exp2f(m - mn), b = exp2f(m2 - mn);
         all = all * a + all2 * b;
         mid = mid * a + mid2 * b;
@@ -40,6 +45,9 @@ struct MamSum {
     // 0 where nothing was summed; a NaN among the logits reaches the mass
     __device__ float mass() const { return all == 0.f ? 0.f : mid / all; }
 };
+
+// Whether a request of n blocks has middle blocks; without any its mass is 0, whatever the logits are.
+__device__ inline bool has_middle(int n, int n_sink, int n_local) { return n_sink < n - n_local; }
 
 // Mean of the G heads' masses, summed in ascending order; lane g holds head g's.
 __device__ inline float mean_mass(float mass, int G) {
@@ -168,7 +176,7 @@ __global__ __launch_bounds__(kMamWaves * kWave) void mam_kernel(
     for (int w = 0; w < kMamWaves; ++w) tot.merge(s_part[w][col].x, s_part[w][col].y, s_part[w][col].z);
     if (n_wg == 1) {
         const float mean = mean_mass(tot.mass(), G);
-        if (lane == 0) mam[(size_t)r * Hkv + h] = mean;
+        if (lane == 0) mam[(size_t)r * Hkv + h] = has_middle(n, n_sink, n_local) ? mean : 0.f;
     } else if (lane < G) {
         part[(((size_t)r * Hkv + h) * n_wg + wg) * G + lane] = make_float4(tot.m, tot.all, tot.mid, 0.f);
     }
@@ -183,6 +191,7 @@ constexpr int kMamMergeThreads = 512;
 __global__ __launch_bounds__(kMamMergeThreads) void mam_merge_kernel(const float4* __restrict__ part, int32_t n_wg,
                                                                      const int32_t* __restrict__ ctx_len, int32_t bs,
                                                                      int32_t max_blocks, int32_t epw, int32_t G,
+                                                                     int32_t n_sink, int32_t n_local,
                                                                      float* __restrict__ mam) {
     constexpr int kStreams = kMamMergeThreads / kMaxGroup;
     __shared__ float4 s_part[kMamMergeThreads / kWave][kMaxGroup];
@@ -210,7 +219,7 @@ __global__ __launch_bounds__(kMamMergeThreads) void mam_merge_kernel(const float
     MamSum tot;
     for (int w = 0; w < kMamMergeThreads / kWave; ++w) tot.merge(s_part[w][g].x, s_part[w][g].y, s_part[w][g].z);
     const float mean = mean_mass(tot.mass(), G);
-    if (lane == 0) mam[(size_t)r * Hkv + h] = mean;
+    if (lane == 0) mam[(size_t)r * Hkv + h] = has_middle((int)n, n_sink, n_local) ? mean : 0.f;
 }
 
 MamPlan mam_plan(int32_t B, int32_t Hkv, int32_t max_blocks, int32_t bs) {
@@ -252,7 +261,7 @@ hipError_t launch_mam(const pulse_shape& s, const void* q, const void* pool, int
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.n_wg == 1) return e;
     hipLaunchKernelGGL(mam_merge_kernel, dim3((unsigned)Hkv, (unsigned)B), dim3(kMamMergeThreads), 0, st, (const float4*)part,
-                       p.n_wg, ctx_len, s.block_size, max_blocks, p.entries_per_wave, G, mam);
+                       p.n_wg, ctx_len, s.block_size, max_blocks, p.entries_per_wave, G, n_sink, n_local, mam);
     return hipGetLastError();
 }
 

@@ -91,6 +91,37 @@ def test_mam_of_non_finite_keys_is_nan(ctx, bad):
     assert out.isnan().cpu().tolist() == [[False, False], [False, True]]
 
 
+# Whole parts of a context whose every logit is NaN: the last workgroup's only token, a wave's blocks, a
+# workgroup's, several workgroups' (those that a thread of the merge starts with), everything; first and last.
+@pytest.mark.parametrize("ctx,lo,hi", [(257, 256, 257), (257, 0, 64), (257, 0, 256), (200, 0, 64), (4096, 0, 64),
+                                       (4096, 0, 256), (4096, 3840, 4096), (16384, 0, 8192), (300, 0, 300)])
+@pytest.mark.parametrize("what", ["key", "query"])
+def test_mam_nan_parts(ctx, lo, hi, what):
+    """A NaN logit makes its head's mass NaN wherever in the merge it stands, in no other head or request."""
+    say(f"\n[gpu] mam NaN {what} ctx={ctx} {lo}..{hi}")
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(ctx + lo)
+    pool, table, ctx_len, n, mb = _paged([ctx, ctx], 2, 16, torch.bfloat16, gen)
+    q = torch.randn((2, 8, D), generator=gen, device=DEV, dtype=torch.bfloat16)
+    sh = P.make_shape(8, 2, D, 16, P.PULSE_BF16)
+    if what == "key":  # tokens lo..hi of request 1, head 1
+        for t in range(lo, hi):
+            pool[table[1, t // 16].long(), 0, 1, (t % 16) * D] = float("nan")
+    else:
+        q[1, 6, 5] = float("nan")  # a query of head 1: every logit of it
+    st = torch.zeros(1, dtype=torch.int32, device=DEV)
+    nb = P.pulse_mam_workspace_bytes(sh, 2, mb)
+    ws = torch.zeros(nb, dtype=torch.uint8, device=DEV)
+    for ns, nl in ((1, 2), (n[0], 0)):  # with middle blocks; without any the mass is 0 whatever the logits are
+        out = torch.full((2, 2), -1.0, device=DEV)
+        P.pulse_mam(sh, q, pool, pool.shape[0], table, mb, ctx_len, 2, ns, nl, D ** -0.5, out, st, ws, nb)
+        assert st.item() == 0
+        if ns == 1:
+            assert out.isnan().cpu().tolist() == [[False, False], [False, True]]
+        else:
+            assert (out == 0).all()
+
+
 # Rows of the FFN products per tile count (16, 32, 64 and beyond), hidden sizes below one group of
 # K steps, with a last step of 8 elements, and on either side of the two-tile rule (512 column tiles).
 FFN_CASES = [(1, 8, 2, 1, 100), (16, 24, 4, 2, 33), (17, 136, 8, 8, 16), (32, 1000, 4, 4, 300), (33, 512, 6, 3, 20),
