@@ -476,6 +476,9 @@ PULSE_API pulse_status pulse_decode_layer_noalloc(const pulse_layer_args* args, 
  *   w_gate_up bf16 [2 d_ff][D] (gate rows, then up rows); w_down bf16 [D][d_ff];
  *   x, gu, h, y bf16 scratch / output of the sizes above; out, lse as for
  *   pulse_sparse_decode_attn; ws pulse_workspace_bytes(shape, B, k_max, 0).
+ * h may share memory with x, and x with the attention's inputs, its ws or lse:
+ * each such layer casts or multiplies in a launch of its own, with the same
+ * results.  gu may not share memory with x or h, nor x with out, nor h with y.
  * The GEMMs (the library's MFMA kernel) read 16-byte pieces of rows: d_ff must
  * be a multiple of 8 (else PULSE_ERR_UNSUPPORTED) and w_gate_up, w_down, x and
  * h 16-byte aligned (else PULSE_ERR_INVALID_ARG).

@@ -49,6 +49,23 @@ __global__ void irq_signal_kernel(int64_t* flag, int64_t value) {
         __hip_atomic_store(flag, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+__device__ inline __bf16 swiglu(float g, float u) { return (__bf16)(g / (1.f + expf(-g)) * u); }
+
+// x = bf16(out) and h = silu(g) * u in launches of their own: for layers whose x or h shares memory with what the
+// attention or the gate and up product, which write them otherwise, still read.
+__global__ __launch_bounds__(256) void to_bf16_kernel(const float* in, __bf16* out, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) out[i] = (__bf16)in[i];
+}
+
+__global__ __launch_bounds__(256) void swiglu_kernel(const __bf16* gu, __bf16* h, int32_t F, int64_t n) {
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+        const int64_t b = i / F, c = i % F;
+        h[i] = swiglu((float)gu[b * 2 * F + c], (float)gu[b * 2 * F + F + c]);
+    }
+}
+
+static unsigned grid_for(int64_t n) { return (unsigned)((n < 4096 * 256 ? n + 255 : 4096 * 256) / 256); }
+
 // ---- the FFN's GEMMs ------------------------------------------------------
 // C[M][N] = A[M][K] . Wt[N][K]^T with bf16 inputs, fp32 accumulation and a bf16
 // (round-to-nearest-even) result: the shape of a decode batch's projections,
@@ -220,15 +237,15 @@ __global__ __launch_bounds__(WV * kWave) void ffn_gemm_kernel(const __bf16* __re
             const __bf16 gb = (__bf16)sum[0], ub = (__bf16)sum[1];
             C[(size_t)m * 2 * N + nn] = gb;
             C[(size_t)m * 2 * N + N + nn] = ub;
-            const float g = (float)gb, u = (float)ub;
-            H[(size_t)m * N + nn] = (__bf16)(g / (1.f + expf(-g)) * u);
+            if (H) H[(size_t)m * N + nn] = swiglu((float)gb, (float)ub);
         } else {
             C[(size_t)m * N + nn] = (__bf16)sum[0];
         }
     }
 }
 
-// PAIR: gu [M][2N] = A . Wt^T for the N gate and N up rows of Wt, H [M][N] = silu(g) * u of the rounded values.
+// PAIR: gu [M][2N] = A . Wt^T for the N gate and N up rows of Wt, H [M][N] (optional) = silu(g) * u of the rounded
+// values.
 //
 // Tiles, at 32 rows (M <= 32; larger M reads the weights once per 64 rows):
 //   gate and up, 4096 -> 2 x 14336 (235 MB): two tiles of each per workgroup of 4 waves, so that the activations
@@ -312,19 +329,48 @@ static pulse_status check_normal(const pulse_normal_layer* n) {
     return PULSE_OK;
 }
 
+static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+    return a && b && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
+// Whether x shares memory with what the attention reads, or writes beside it.
+static bool x_under_attention(const pulse_normal_layer& n, size_t x_bytes, size_t ws_used) {
+    const size_t B = (size_t)n.B, i32 = sizeof(int32_t);
+    auto at = [&](const void* p, size_t bytes) { return overlap(n.x, x_bytes, p, bytes); };
+    return at(n.q, x_bytes) || at(n.slot_pool, (size_t)n.n_slots * pulse_block_bytes(&n.shape)) ||
+           at(n.block_table, i32 * B * n.max_blocks) || at(n.sel_idx, i32 * B * n.k_max) || at(n.sel_cnt, i32 * B) ||
+           at(n.ctx_len, i32 * B) || at(n.lse, sizeof(float) * B * n.shape.num_q_heads) || at(n.ws, ws_used);
+}
+
 // Enqueue one normal-batch layer on irq->cmp; ev_attn (optional) is recorded after its
 // attention, ev_end (optional) after its FFN.
 static pulse_status normal_layer(pulse_irq* irq, const pulse_normal_layer& n, hipEvent_t ev_attn, hipEvent_t ev_end) {
     const hipStream_t hs = irq->cmp;
     const WsLayout w = ws_layout(n.shape, n.B, n.k_max, 0);
+    const int32_t D = n.shape.num_q_heads * n.shape.head_dim, F = n.d_ff, B = n.B;
+    // x is written by the attention and h by the gate and up product, unless others still read that memory then
+    const size_t x_bytes = (size_t)B * D * 2;
+    const bool own_cast = x_under_attention(n, x_bytes, w.total);
+    const bool own_swiglu = overlap(n.x, x_bytes, n.h, (size_t)B * F * 2);
     if (launch_attention(n.shape, n.q, n.slot_pool, n.n_slots, n.block_table, n.max_blocks, n.sel_idx, n.sel_cnt,
                          n.k_max, n.ctx_len, n.B, n.sm_scale, n.out, n.lse, ws_at<float>(n.ws, w.attn_o),
-                         ws_at<float2>(n.ws, w.attn_ml), n.dev_status, hs, nullptr, nullptr, (__bf16*)n.x) != hipSuccess)
+                         ws_at<float2>(n.ws, w.attn_ml), n.dev_status, hs, nullptr, nullptr,
+                         own_cast ? nullptr : (__bf16*)n.x) != hipSuccess)
         return PULSE_ERR_HIP;
     if (ev_attn && hipEventRecord(ev_attn, hs) != hipSuccess) return PULSE_ERR_HIP;
-    const int32_t D = n.shape.num_q_heads * n.shape.head_dim, F = n.d_ff, B = n.B;
+    if (own_cast) {
+        const int64_t nx = (int64_t)B * D;
+        hipLaunchKernelGGL(to_bf16_kernel, dim3(grid_for(nx)), dim3(256), 0, hs, n.out, (__bf16*)n.x, nx);
+        if (hipGetLastError() != hipSuccess) return PULSE_ERR_HIP;
+    }
     // gu [B][2F] = x [B][D] . W_gu^T, h [B][F] = silu(g) * u
-    if (launch_ffn_gemm<true>(n.x, n.w_gate_up, n.gu, n.h, B, F, D, hs) != hipSuccess) return PULSE_ERR_HIP;
+    if (launch_ffn_gemm<true>(n.x, n.w_gate_up, n.gu, own_swiglu ? nullptr : n.h, B, F, D, hs) != hipSuccess)
+        return PULSE_ERR_HIP;
+    if (own_swiglu) {
+        const int64_t nh = (int64_t)B * F;
+        hipLaunchKernelGGL(swiglu_kernel, dim3(grid_for(nh)), dim3(256), 0, hs, (const __bf16*)n.gu, (__bf16*)n.h, F, nh);
+        if (hipGetLastError() != hipSuccess) return PULSE_ERR_HIP;
+    }
     // y [B][D] = h [B][F] . W_down^T
     if (launch_ffn_gemm<false>(n.h, n.w_down, n.y, nullptr, B, D, F, hs) != hipSuccess) return PULSE_ERR_HIP;
     if (ev_end && hipEventRecord(ev_end, hs) != hipSuccess) return PULSE_ERR_HIP;

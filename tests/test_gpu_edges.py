@@ -164,6 +164,54 @@ def test_normal_layer_edges(B, F, hq, hkv, ctx):
     sched.destroy()
 
 
+@pytest.mark.parametrize("ctx", [40, 900])  # one workgroup per head (it writes the output), several and a merge
+@pytest.mark.parametrize("how", ["h on x", "h past x", "x in ws", "x on q", "x past q", "x on lse"])
+def test_normal_layer_shared_buffers(ctx, how):
+    """A layer whose x or h lies in memory that is read before it is written gives what separate buffers give."""
+    from paper_2609_34555_amd.harness import NormalBatch
+    from paper_2609_34555_amd import workloads as W
+    from parity import build
+
+    say(f"\n[gpu] normal layer ctx={ctx} {how}")
+    spec, seed = W.custom("light", [200], Hq=4, Hkv=2, bs=16, k_mid=2)
+    w, st = build(spec, seed)
+    B, hq, F = 6, 8, 1032
+    normal = NormalBatch(B=B, ctx=ctx, n_layers=1, Hq=hq, Hkv=2, d_ff=F, seed=3)
+    b, layer = normal.bufs[0], normal.layers[0]
+    nx, nh, nq = 2 * B * hq * D, 2 * B * F, 2 * B * hq * D
+    cmp_, io = torch.cuda.Stream(), torch.cuda.Stream()
+    sched = P.IrqScheduler(cmp_, io)
+
+    def step():
+        st.reset()
+        torch.cuda.synchronize()
+        sched.step([st.layer_args()], normal.layers, mode="blocking")
+        torch.cuda.synchronize()
+        assert normal.status() == 0 and st.status() == 0
+
+    step()
+    want = {k: b[k].clone() for k in ("out", "gu", "h", "y", "x")}
+    mem = torch.full((nx + nh + nq + normal.ws_bytes + 4096,), 255, dtype=torch.uint8, device=DEV)
+    q = b["q"].view(torch.uint8).view(-1)
+    if how[0] == "h":
+        layer.x, layer.h = mem.data_ptr(), mem.data_ptr() + (0 if how == "h on x" else nx // 2)
+    elif how == "x in ws":
+        layer.ws, layer.x = mem.data_ptr(), mem.data_ptr() + 1024
+        assert nx + 1024 < normal.ws_bytes
+    elif how == "x on lse":
+        layer.lse = layer.x = mem.data_ptr()
+    else:
+        mem[:nq] = q
+        layer.q, layer.x = mem.data_ptr(), mem.data_ptr() + (0 if how == "x on q" else nq // 2)
+    step()
+    for k in ("out", "gu", "y"):
+        assert torch.equal(b[k], want[k]), k
+    at = (layer.x if how[0] == "x" else layer.h) - mem.data_ptr()
+    last = want["x" if how[0] == "x" else "h"]
+    assert torch.equal(mem[at:at + 2 * last.numel()].view(torch.bfloat16), last.view(-1))
+    sched.destroy()
+
+
 # Selected blocks per request around the shares of the split plan: equal, one long request among short and
 # empty ones, the plan's limit of 64 requests and one past it, many heads per KV head (4-wave workgroups).
 PLAN_CASES = [
