@@ -260,8 +260,6 @@ def test_attention_split_plan(cnt, hq, hkv, bs, dt):
             assert (lse[r, h * G:(h + 1) * G] - torch.logsumexp(s, 1)).abs().max() < 1e-5, (r, h)
 
 
-# Average scores: one head, head counts that divide a workgroup's 16 pairs and that do not, more than 16
-# heads, ragged and empty requests, and more digests than the one-launch limit (65536).
 @pytest.mark.parametrize("hkv", [1, 8, 257])
 def test_average_of_no_blocks(hkv):
     """Requests without blocks select nothing, whatever the head count."""
@@ -275,6 +273,8 @@ def test_average_of_no_blocks(hkv):
     assert st.item() == 0 and (cnt == 0).all() and (sel == -1).all()
 
 
+# Average scores: one head, head counts that divide a workgroup's 16 pairs and that do not, more than 16
+# heads, ragged and empty requests, and more digests than the one-launch limit (65536).
 AVG_EDGES = [([300, 0, 17], 8, 1, "bf16"), ([700, 31, 0, 0, 650], 6, 3, "f16"), ([900, 2000], 32, 8, "bf16"),
              ([1, 16, 4000], 20, 5, "bf16"), ([500, 900], 34, 17, "f16"), ([131072, 7000], 32, 8, "bf16")]
 
@@ -367,6 +367,115 @@ def test_select_block_counts(n, copies):
             ids = torch.cat([torch.arange(lo, device=DEV), top, torch.arange(hi, n[r], device=DEV)]).sort().values
             assert cnt[r].item() == len(ids), (share, r)
             assert torch.equal(sel[r, : len(ids)].long(), ids) and (sel[r, len(ids):] == -1).all(), (share, r)
+
+
+# The plan beside the selection: runs of missing blocks across the one-wave path's 64-block rounds, the general
+# path's waves (64), rounds (1024) and tiles (8192), on either side of the 512 blocks where the paths part.
+@pytest.mark.parametrize("n", [[63, 64, 65], [127, 128, 129, 0, 1], [510, 511, 512], [513, 512, 514], [1023, 1025, 2050],
+                               [8191, 8193], [8193, 300, 9000]])
+@pytest.mark.parametrize("share", [1.0, 0.4])
+def test_select_plan_counts(n, share):
+    say(f"\n[gpu] select plan n={n} share={share}")
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(sum(n))
+    B, H, total, ns, nl, G, n_slots = len(n), 2, sum(n), 1, 2, 4, 1000
+    off = [0]
+    for k in n:
+        off.append(off[-1] + k)
+    a = torch.randn((2, H * total, D), generator=gen, device=DEV, dtype=torch.bfloat16)
+    dig = torch.stack([a.amin(0), a.amax(0)], 1).contiguous()
+    q = torch.randn((B, H * G, D), generator=gen, device=DEV, dtype=torch.bfloat16)
+    i32 = dict(dtype=torch.int32, device=DEV)
+    blk_off = torch.tensor(off, dtype=torch.int64, device=DEV)
+    mb, k_max = max(n), max(n)
+    table = torch.randint(0, n_slots, (B, mb), generator=gen, **i32)
+    for at in range(0, mb, 64):  # missing around every 64th block, and a long run over several rounds
+        table[:, max(0, at - 3):at + at // 64 % 5] = -1
+    table[:, 300:480] = -1
+    table[:, 1000:1300] = -1
+    sh = P.make_shape(H * G, H, D, 16, P.PULSE_BF16)
+    nb = P.pulse_headwise_workspace_bytes(sh, B, k_max, total)
+    ws = torch.zeros(nb, dtype=torch.uint8, device=DEV)
+
+    def select(k_mid, k_max, table):
+        sel, cnt = torch.full((H, B, k_max), -7, **i32), torch.full((H, B), -7, **i32)
+        miss, run, st = torch.full((H, B), -7, **i32), torch.full((H, B), -7, **i32), torch.zeros(1, **i32)
+        P.pulse_select_headwise(sh, q, dig, blk_off, B, total, torch.tensor(k_mid, **i32), ns, nl, k_max, table, mb,
+                                n_slots, sel, cnt, miss, run, st, ws, nb)
+        return sel.cpu(), cnt.cpu(), miss.cpu(), run.cpu(), st.item()
+
+    k_mid = [int(share * x) for x in n]
+    sel, cnt, miss, run, st = select(k_mid, k_max, table)
+    assert st == 0
+    tab = table.cpu()
+    for h in range(H):
+        for r in range(B):
+            forced = len(set(range(min(ns, n[r]))) | set(range(max(0, n[r] - nl), n[r])))
+            c = forced + min(k_mid[r], n[r] - forced)
+            assert cnt[h, r] == c and (sel[h, r, c:] == -1).all()
+            ids = sel[h, r, :c].long()
+            m = ids[tab[r, ids] < 0]
+            assert miss[h, r] == len(m), (h, r)
+            assert run[h, r] == int((m[1:] != m[:-1] + 1).sum()) + (len(m) > 0), (h, r)
+    # a selected entry past the pool is reported, an unselected one is not
+    bad = table.clone()
+    big = max(range(B), key=lambda r: n[r])
+    bad[big, n[big] - 1] = n_slots  # a local block
+    assert select(k_mid, k_max, bad)[4] == P.PULSE_ERR_BAD_INDEX
+    bad = table.clone()
+    bad[big, n[big] // 2] = n_slots
+    assert select([0] * B, k_max, bad)[4] == 0
+    # one block too many: that request (and any other of its count) is empty, the rest are as they were
+    limit = int(cnt[0, big]) - 1
+    full = (sel, cnt, miss, run)
+    sel, cnt, miss, run, st = select(k_mid, limit, table)
+    assert st == P.PULSE_ERR_SELECT_OVERFLOW
+    for r in range(B):
+        if full[1][0, r] > limit:
+            assert (cnt[:, r] == 0).all() and (sel[:, r] == -1).all() and (miss[:, r] == 0).all() and (run[:, r] == 0).all()
+        else:
+            assert torch.equal(sel[:, r], full[0][:, r, :limit])
+            assert all(torch.equal(a[:, r], b[:, r]) for a, b in zip((cnt, miss, run), full[1:]))
+
+
+# The layer-step on requests past the one-wave selection: lengths for which the loads at equal-length offsets
+# are right for requests 0 and 3 and wrong for 1 and 2, then lengths on both sides of 512 blocks and of a tile.
+@pytest.mark.parametrize("n", [[800, 1120, 480, 800], [600, 500, 513, 512], [8300, 700, 100]])
+@pytest.mark.parametrize("fault", ["none", "overflow", "entry past pool"])
+def test_chained_layer_longer_requests(n, fault):
+    from oracle import pulse_oracle as O
+    from paper_2609_34555_amd import workloads as W
+    from parity import (assert_attention_close, assert_recall_equal, assert_selection_ok, build, full_check,
+                        oracle_attention, oracle_recall, oracle_selection)
+    import numpy as np
+
+    say(f"\n[gpu] chained n={n} {fault}")
+    spec, seed = W.custom("longer", [16 * x - r for r, x in enumerate(n)], Hq=4, Hkv=1, bs=16, dtype="bf16",
+                          k_mid=[20, 40, 9, 50][:len(n)], n_sink=1, n_local=8, resident_frac=0.1, heavy_per_req=6)
+    w, st = build(spec, seed, k_max=48 if fault == "overflow" else None)
+    if fault == "none":
+        full_check(w, st, chained=True)
+        return
+    st.reset()
+    table0 = w.table0.copy()
+    if fault == "entry past pool":
+        table0[0, n[0] - 1] = w.n_slots  # a local block, always selected
+        st.table.copy_(torch.from_numpy(table0))
+    st.decode_layer()
+    torch.cuda.synchronize()
+    code, ocode = ((P.PULSE_ERR_SELECT_OVERFLOW, O.ERR_SELECT_OVERFLOW) if fault == "overflow"
+                   else (P.PULSE_ERR_BAD_INDEX, O.ERR_BAD_INDEX))
+    assert st.status() == code
+    gidx, gcnt = st.selection()
+    dig = st.digests.cpu().numpy().view(np.uint16)[: w.total_blocks]
+    rc, oidx, ocnt, osc = oracle_selection(w, dig, k_max=st.k_max)
+    assert_selection_ok(w, gidx, gcnt, oidx, ocnt, osc)
+    rr, table, pool, fh, stats = oracle_recall(w, gidx, gcnt, table0=table0)
+    assert (rc if fault == "overflow" else rr) == ocode
+    assert_recall_equal(st, table, pool, fh, stats)
+    if fault == "overflow":
+        assert gcnt[1] == 0 and stats[0] > 0
+        assert_attention_close(st, *oracle_attention(w, pool, table, gidx, gcnt))
 
 
 def test_irq_blocking_step_follows_io_stream_work():
