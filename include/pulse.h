@@ -344,7 +344,10 @@ PULSE_API pulse_status pulse_gs_last_timing(pulse_gs_engine* engine, float* ms3)
  *   out[r][hq] = sum_t softmax(logit)_t V(h, t)      (fp32)
  *   lse[r][hq] = log sum_t exp(logit_t)              (fp32, optional)
  * An empty selection gives out = 0 and lse = -inf.  Products and sums are
- * accumulated in fp32.
+ * accumulated in fp32.  The order of a request's sums depends on B, Hkv, k_max
+ * and bs and, for 2 to 64 requests whose counts are not all k_max, on every
+ * request's sel_cnt: the last bits of a request's results may change with its
+ * neighbours' counts.  The same call repeats its bits.
  *   out          device float [B][Hq][d];  lse optional device float [B][Hq]
  *   dev_status   device int32, required (unresident block -> BAD_INDEX)
  */
