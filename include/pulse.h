@@ -529,7 +529,8 @@ typedef struct pulse_irq_stats {
     double wall_ms;             /* host wall time of the step, all work finished */
     double mean_stall_us;       /* GPU time from a layer's selection to its attention: the offload batch parked */
     double mean_resume_us;      /* gather kernel path: GPU time from a recall's completion to its attention */
-    double mean_recall_us;      /* gather kernel path: GPU time of a recall (copy + completion signal) */
+    double mean_recall_us;      /* gather kernel path: GPU time of a recall (copy + completion signal; BLOCKING
+                                   sends no signal: the copy) */
 } pulse_irq_stats;
 
 typedef struct pulse_irq pulse_irq;
@@ -567,7 +568,8 @@ PULSE_API pulse_status pulse_irq_destroy(pulse_irq* irq);
  * layers run during each recall; stats is filled (host).  Returns after both
  * streams (and, after an early exit, an engine call in flight) are drained.
  * A recall whose flag is not seen within 60 s ends the step with
- * PULSE_ERR_TIMEOUT (after draining); device-side errors are in the layers'
+ * PULSE_ERR_TIMEOUT (after draining); BLOCKING without an engine looks at no
+ * flag and has no such limit.  Device-side errors are in the layers'
  * dev_status words.
  */
 PULSE_API pulse_status pulse_irq_step(pulse_irq* irq, const pulse_layer_args* offload, int32_t n_offload_layers,
