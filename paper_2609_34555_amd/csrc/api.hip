@@ -191,10 +191,8 @@ pulse_status pulse_select_average(const pulse_shape* shape, const void* q, const
     const size_t heads = sizeof(float) * (size_t)shape->num_kv_heads * (size_t)total_blocks;
     float* avg = scores ? scores : at<float>(ws, align_up(heads));
     hipStream_t hs = (hipStream_t)stream;
-    hipError_t e = hipSuccess;
-    if (total_blocks > 0)
-        e = launch_average_scores(*shape, q, head_digests, blk_off, B, total_blocks, n_sink_blocks, n_local_blocks, avg,
-                                  at<float>(ws, 0), hs);
+    hipError_t e = launch_average_scores(*shape, q, head_digests, blk_off, B, total_blocks, n_sink_blocks,
+                                         n_local_blocks, avg, at<float>(ws, 0), hs);
     if (e != hipSuccess) return PULSE_ERR_HIP;
     e = launch_select(blk_off, B, total_blocks, avg, k_mid, n_sink_blocks, n_local_blocks, k_max, sel_idx, sel_cnt,
                       nullptr, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, dev_status, 1, hs);

@@ -413,13 +413,14 @@ static void launch_average_dt(int G, hipStream_t st, const void* q, const void* 
 }
 
 // One head: its scores are the average.  Up to kScoreLargeBlocks digests one launch scores and
-// averages (8 heads x 256 blocks 15.9 -> 11.9 us with the selection, 2 heads x 8450 15.7 ->
+// averages (8 heads x 256 blocks 15.5 -> 11.7 us with the selection, 2 heads x 8450 15.7 ->
 // 12.3); larger sets stream better with neighbouring workgroups on one head's digests, so every
 // head scores into ws first (8 heads x 65536 blocks: 43 us and 3 of averaging; in one launch
 // 47 to 60, whether groups took heads in turn or pairs of up to 8 blocks and 8 heads).
 hipError_t launch_average_scores(const pulse_shape& s, const void* q, const void* digests, const int64_t* blk_off,
                                  int32_t B, int64_t total_blocks, int32_t n_sink, int32_t n_local, float* scores,
                                  float* head_scores, hipStream_t st) {
+    if (total_blocks == 0) return hipSuccess;
     if (s.num_kv_heads == 1)
         return launch_score(s, q, digests, blk_off, B, total_blocks, 0, n_sink, n_local, scores, 1, st);
     // (the one launch holds a block's scores of every head in LDS)
@@ -432,7 +433,6 @@ hipError_t launch_average_scores(const pulse_shape& s, const void* q, const void
                            s.num_kv_heads, n_sink, n_local, scores);
         return hipGetLastError();
     }
-    if (total_blocks == 0) return hipSuccess;
     const int32_t H = s.num_kv_heads, G = s.num_q_heads / H;
     if (s.dtype == PULSE_BF16)
         launch_average_dt<PULSE_BF16>(G, st, q, digests, blk_off, B, total_blocks, s.num_q_heads, H, n_sink, n_local,
