@@ -199,9 +199,9 @@ pulse_status pulse_select_average(const pulse_shape* shape, const void* q, const
     return hip_status(e);
 }
 
-// MAM workspace: the partials of the context pass.  The size keeps room for an attention's scratch, two
-// selections, an output and two lse arrays, which callers already allocate by; the partials (16 bytes per
-// workgroup and query head) are far smaller.
+// MAM workspace: the partials of the context pass, 16 bytes per workgroup and query head.  The size is that of the two
+// attentions, with selections, an output and lse, that the call once ran (a test keeps it as the least); the partials
+// take a small part of it.
 static size_t mam_ws_bytes(const pulse_shape& s, int32_t B, int32_t max_blocks) {
     size_t o = ws_layout(s, B, max_blocks, 0).total;
     for (int i = 0; i < 2; ++i) {

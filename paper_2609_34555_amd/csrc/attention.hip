@@ -58,13 +58,15 @@ struct SplitArgs {
 // device; where they differ, that leaves long requests few waves and short ones idle
 // workgroups, so the kernels share the same grid out by the counts: the least eps with
 // which ceil(cnt / (W * eps)) workgroups per request and head fit the grid, and at
-// least the length that would give kTargetWaves waves in all.  Workgroup p is piece
+// least the length that would give PULSE_ATTN_TARGET_WAVES waves in all.  Workgroup p is piece
 // (p / Hkv, head p % Hkv) of the requests' pieces in order; its partial is number p.
 // Taken for up to 64 requests (one lane each) when a request may have several
 // workgroups: at 16 requests x 65K tokens with budgets of 317 to 8192 tokens (lognormal
-// around 2048) 58.2 us before, 42.6 with it (188 MB; the split kernel at 5.7 TB/s).  Equal counts
-// keep the host's own split: 8 x 2048 tokens 16.2 us (16.7 with splits numbered before heads, as
-// before), 4 x 8192 at G 8 30.2 (30.4); both HBM-bound between their first key and last value.
+// around 2048), four batches in turn, 58.1 us before, 42.5 with it (188 MB; the split kernel at
+// 5.7 TB/s).  Equal counts keep the host's own split: 8 x 2048 tokens 16.2 us (16.7 with splits
+// numbered before heads, as before), 4 x 8192 at G 8 30.2 (30.4), memory-bound between their first
+// key and last value.  (67 and 134 MB, which stay in the 256 MB Infinity Cache when one batch is
+// repeated; batches in turn, all steps together: 19.5 -> 19.0 and 30.5 -> 30.0.)
 constexpr int kPlanRequests = 64;
 
 struct Piece {
@@ -203,8 +205,9 @@ __device__ inline void attend_split(const uint16_t* __restrict__ q, const uint16
     };
 
     // One 32-token step at a time: K is loaded first, V once the S tile is issued, so
-    // the V loads overlap the softmax and fewer operands are live (125 VGPRs, 4 waves
-    // per SIMD).  The other resident waves hide the load latency.  Measured slower:
+    // the V loads overlap the softmax and fewer operands are live (121-128 VGPRs and 4
+    // waves per SIMD with 8-wave workgroups, up to 130 and 3 with 4-wave ones).  The
+    // other resident waves hide the load latency.  Measured slower:
     // loading K and V together (154 VGPRs; 2-5%), prefetching the next step into
     // registers as well (223 VGPRs; another 1-2%), and, for splits of two steps,
     // issuing all four loads before the first product (177 VGPRs; 11% slower on

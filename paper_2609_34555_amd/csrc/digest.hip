@@ -36,8 +36,9 @@ __device__ inline s16x2 order16(s16x2 x) { return x ^ ((x >> 15) & (int16_t)0x7F
 // on the request, so the whole block is loaded first (BS / 4 loads of 16 bytes in flight per
 // lane) and the request is looked up meanwhile; rows past the context are left out of the
 // minimum and maximum.  Both are taken on packed pairs: with one value per register the
-// vector instructions bound the kernel.  8 x 32K tokens, 8 KV heads (73 MB): 21.2 us with
-// both the look-up first and single values, 15.9 now (4.6 TB/s).
+// vector instructions bound the kernel.  8 x 32K tokens, 8 KV heads (73 MB), six batches in
+// turn: 24.2 us with both the look-up first and single values, 17.6 now (4.2 TB/s).  One batch
+// over and over, whose keys stay in the 256 MB Infinity Cache: 18.0 and 14.7.
 template <int BS>
 __global__ __launch_bounds__(256) void build_digests_kernel(const uint16_t* __restrict__ kv,
                                                             const int64_t* __restrict__ blk_off,

@@ -54,7 +54,8 @@ __device__ inline __bf16 swiglu(float g, float u) { return (__bf16)(g / (1.f + e
 // x = bf16(out) and h = silu(g) * u in launches of their own: for layers whose x or h shares memory with what the
 // attention or the gate and up product, which write them otherwise, still read.
 __global__ __launch_bounds__(256) void to_bf16_kernel(const float* in, __bf16* out, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) out[i] = (__bf16)in[i];
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+        out[i] = (__bf16)in[i];
 }
 
 __global__ __launch_bounds__(256) void swiglu_kernel(const __bf16* gu, __bf16* h, int32_t F, int64_t n) {
@@ -254,6 +255,9 @@ __global__ __launch_bounds__(WV * kWave) void ffn_gemm_kernel(const __bf16* __re
 //   down, 14336 -> 4096 (117 MB): one tile, 8 waves, steps of 4: 27.8 us (4.2 TB/s); two tiles (half the CUs) 34.7;
 //   steps of 2 29.9, 16 waves in steps of 2 30.8.
 // The form before, operands loaded in their layout: 61.4 us + 4.8 of a SwiGLU kernel, and 49.7.
+// Above 32 rows four row tiles and one column tile, 8 waves in steps of 2 (96 and 80 KiB of LDS, one workgroup per
+// CU): at 64 rows gate and up 63.3 us (3.7 TB/s), down 42.2, before 148.3 + 5.1 and 78.0; at 256 rows, the weights
+// read four times, 231 and 162, before 593 + 10 and 307.
 template <bool PAIR>
 static hipError_t launch_ffn_gemm(const void* A, const void* Wt, void* C, void* H, int32_t M, int32_t N, int32_t K,
                                   hipStream_t st) {
@@ -368,7 +372,8 @@ static pulse_status normal_layer(pulse_irq* irq, const pulse_normal_layer& n, hi
         return PULSE_ERR_HIP;
     if (own_swiglu) {
         const int64_t nh = (int64_t)B * F;
-        hipLaunchKernelGGL(swiglu_kernel, dim3(grid_for(nh)), dim3(256), 0, hs, (const __bf16*)n.gu, (__bf16*)n.h, F, nh);
+        hipLaunchKernelGGL(swiglu_kernel, dim3(grid_for(nh)), dim3(256), 0, hs, (const __bf16*)n.gu, (__bf16*)n.h, F,
+                           nh);
         if (hipGetLastError() != hipSuccess) return PULSE_ERR_HIP;
     }
     // y [B][D] = h [B][F] . W_down^T
