@@ -345,8 +345,8 @@ PULSE_API pulse_status pulse_gs_last_timing(pulse_gs_engine* engine, float* ms3)
  *   lse[r][hq] = log sum_t exp(logit_t)              (fp32, optional)
  * An empty selection gives out = 0 and lse = -inf.  Products and sums are
  * accumulated in fp32.  The order of a request's sums depends on B, Hkv, k_max
- * and bs and, for 2 to 64 requests whose counts are not all k_max, on every
- * request's sel_cnt: the last bits of a request's results may change with its
+ * and bs and, for 2 to 64 requests whose counts are not all k_max, may depend on
+ * every request's sel_cnt: the last bits of a request's results may change with its
  * neighbours' counts.  The same call repeats its bits.
  *   out          device float [B][Hq][d];  lse optional device float [B][Hq]
  *   dev_status   device int32, required (unresident block -> BAD_INDEX)
@@ -362,8 +362,8 @@ PULSE_API pulse_status pulse_sparse_decode_attn(const pulse_shape* shape, const 
  * Split-K workgroups per (request, KV head) that pulse_sparse_decode_attn,
  * and the attention of pulse_decode_layer, launch for a batch of B requests
  * with at most k_max selected blocks each (it depends on B, Hkv, k_max and bs
- * only; up to 64 requests whose counts differ share these workgroups out by
- * their counts).  Above 1, a kernel that merges the workgroups' partials
+ * only; up to 64 requests whose counts differ may share these workgroups out
+ * by their counts).  Above 1, a kernel that merges the workgroups' partials
  * follows the split-K kernel, and pulse_layer_args.attn_split_event marks the
  * end of the split-K kernel alone.  At 1, one workgroup covers each (request,
  * KV head) and writes out / lse itself: no merge kernel runs, so a caller that

@@ -49,7 +49,9 @@ static int32_t split_least(int32_t bs) { return bs >= 2 * kChunkTokens ? 1 : 2 *
 struct SplitArgs {
     int32_t eps, n_wg;    // host plan: entries per wave, workgroups per (request, KV head)
     int32_t step, least;  // granularity and least value of eps
+    int32_t fit;          // pieces that a plan may have
     bool planned;         // share the grid out by the counts
+    bool light_last;      // every (request, KV head)'s last workgroup has fewer waves: start those last
 };
 
 // ---- the split plan ----
@@ -57,16 +59,26 @@ struct SplitArgs {
 // per (request, KV head), whose W waves take eps entries each.  Counts live on the
 // device; where they differ, that leaves long requests few waves and short ones idle
 // workgroups, so the kernels share the same grid out by the counts: the least eps with
-// which ceil(cnt / (W * eps)) workgroups per request and head fit the grid, and at
-// least the length that would give PULSE_ATTN_TARGET_WAVES waves in all.  Workgroup p is piece
-// (p / Hkv, head p % Hkv) of the requests' pieces in order; its partial is number p.
-// Taken for up to 64 requests (one lane each) when a request may have several
-// workgroups: at 16 requests x 65K tokens with budgets of 317 to 8192 tokens (lognormal
-// around 2048), four batches in turn, 58.1 us before, 42.5 with it (188 MB; the split kernel at
-// 5.7 TB/s).  Equal counts keep the host's own split: 8 x 2048 tokens 16.2 us (16.7 with splits
-// numbered before heads, as before), 4 x 8192 at G 8 30.2 (30.4), memory-bound between their first
-// key and last value.  (67 and 134 MB, which stay in the 256 MB Infinity Cache when one batch is
-// repeated; batches in turn, all steps together: 19.5 -> 19.0 and 30.5 -> 30.0.)
+// which ceil(cnt / (W * eps)) workgroups per request and head are no more than `fit`.
+// Workgroup p is piece (p / Hkv, head p % Hkv) of the requests' pieces in order; its
+// partial is number p.
+//
+// A CU takes a second workgroup only at the cost of both (their loads share its
+// address path), so `fit` is one round of workgroups (2048 waves) where that leaves a
+// quarter more pieces than requests, and the grid otherwise or where the host's own
+// split takes more than a round.  Without a plan, where the grid takes more than a round
+// and every last workgroup has fewer waves, splits are numbered slowest, so that those
+// are the ones that come second.
+// Finding and following a plan costs 1 to 2 us (two memory round trips), so it is for up to
+// 64 requests (one lane each) whose eps may halve, or whose empty workgroups would make a
+// second round.  In us, three batches in turn: the host's split alone (before the reductions
+// in registers), a plan up to the whole grid wherever counts differ, and as it is.  Over 560
+// calls drawn from 1 to 32 requests and budgets of 256 to 8192 tokens, lognormal or equal, the
+// second was 1.08 and this is 1.13 times as fast as the first; 101 and 11 calls lost over 1%.
+//   16 requests x 65K tokens, lognormal around 2048 tokens (188 MB)    58.0  42.7  43.0
+//   7 requests x 120K tokens, blocks of 32, around 2705 (100 MB)       29.4  31.0  23.7
+//   20 requests, 2 KV heads, all 387 blocks (280 workgroups)           34.6  39.0  29.6
+//   5 requests, 3 KV heads, around 702 tokens                          11.3  12.1  11.0
 constexpr int kPlanRequests = 64;
 
 struct Piece {
@@ -78,6 +90,15 @@ struct Piece {
 // Workgroups of a request of c blocks: at least one, which writes an empty request's output.
 __device__ inline int pieces_of(int c, int per) { return max(1, (c + per - 1) / per); }
 
+// The same for c below 2^23, by the reciprocal, whose quotient is at most one off.
+__device__ inline int pieces_short(int c, int per) {
+    const int n = c + per - 1;
+    int q = (int)((float)n * __builtin_amdgcn_rcpf((float)per));
+    const int rest = n - q * per;
+    q += rest < 0 ? -1 : rest >= per ? 1 : 0;
+    return max(1, q);
+}
+
 // Whether every request has k_max blocks (raw: sel_cnt of request `lane`): the host's split as it is.
 __device__ inline bool equal_counts(int32_t raw, int32_t B, int32_t k_max, int lane) {
     return __ballot(lane < B && raw != k_max) == 0;
@@ -85,21 +106,18 @@ __device__ inline bool equal_counts(int32_t raw, int32_t B, int32_t k_max, int l
 
 // Plan for piece index pr (of all heads of a request at once); all lanes of a wave take
 // part.  raw: sel_cnt of request `lane` (B <= kPlanRequests).  r < 0: no such piece.
-__device__ inline Piece plan_piece(int pr, int32_t raw, int32_t B, int32_t k_max, int32_t Hkv, int32_t W,
-                                   int32_t eps0, int32_t n_wg0, int32_t step, int32_t least, int lane) {
+__device__ inline Piece plan_piece(int pr, int32_t raw, int32_t B, int32_t k_max, int32_t W, const SplitArgs& sp,
+                                   int lane) {
     const int c = (lane < B && raw >= 0 && raw <= k_max) ? raw : 0;
     Piece p;
-    p.eps = eps0;
-    auto pieces = [&](int eps) { return lane < B ? (uint32_t)pieces_of(c, W * eps) : 0u; };
-    const uint32_t total = last_lane(wave_scan((uint32_t)c, 0u, OpAdd()));
-    const int64_t waves = PULSE_ATTN_TARGET_WAVES;
-    int lo = (int)(((int64_t)total * Hkv + waves - 1) / waves);
-    lo = max(least, (lo + step - 1) / step * step);
-    int hi = eps0;  // fits: no request has more than n_wg0 workgroups then
+    auto pieces = [&](int eps) { return lane < B ? (uint32_t)pieces_short(c, W * eps) : 0u; };
+    auto sum = [&](int eps) { return (int)last_lane(wave_scan(pieces(eps), 0u, OpAdd())); };
+    const int fit = sum(sp.eps) <= sp.fit ? sp.fit : B * sp.n_wg;
+    int lo = sp.least, hi = sp.eps;  // hi fits: no request has more than n_wg workgroups then
     while (lo < hi) {
-        const int mid = (lo + hi) / 2 / step * step;
-        if (last_lane(wave_scan(pieces(mid), 0u, OpAdd())) <= (uint32_t)B * (uint32_t)n_wg0) hi = mid;
-        else lo = mid + step;
+        const int mid = (lo + hi) / 2 / sp.step * sp.step;
+        if (sum(mid) <= fit) hi = mid;
+        else lo = mid + sp.step;
     }
     p.eps = hi;
     const uint32_t np = pieces(p.eps);
@@ -282,8 +300,8 @@ __device__ inline void attend_split(const uint16_t* __restrict__ q, const uint16
     l_run = across_groups(l_run, [](float a, float b) { return a + b; });
 }
 
-// grid = (Hkv, n_wg0, B): in this order workgroup p is piece p / Hkv of KV head p % Hkv (see the split plan); wave w of a
-// request's workgroup wg owns split W * wg + w of eps entries.  Dynamic LDS: O [W][G][128] floats then
+// grid = (Hkv, n_wg, B), or (Hkv, B, n_wg) with light_last; in either, workgroup p is piece p / Hkv of KV head p % Hkv
+// of a plan; wave w of a request's workgroup wg owns split W * wg + w of eps entries.  Dynamic LDS: O [W][G][128] floats then
 // (m, l) [W][G] float2.
 template <int DT, int BS, int W>
 __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
@@ -299,14 +317,15 @@ __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
     float2* s_ml = reinterpret_cast<float2*>(smem + W * G * kHeadDim);  // [W][G]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, grp = lane >> 4;
-    const int h = blockIdx.x, pr = (int)(blockIdx.z * gridDim.y + blockIdx.y);
+    const int h = blockIdx.x;
 
     // this wave's selected blocks (one per lane) are loaded with the counts they depend on, at the place
     // they have when all counts are equal: one memory round trip fewer before the first K load
     Piece p;
-    p.r = blockIdx.z;
-    p.wg = blockIdx.y;
+    p.r = sp.light_last ? blockIdx.y : blockIdx.z;
+    p.wg = sp.light_last ? blockIdx.z : blockIdx.y;
     p.eps = sp.eps;
+    int piece = p.r * sp.n_wg + p.wg;
     const bool planned = sp.planned;
     auto load_j = [&]() {
         const int e = (p.wg * W + wave) * p.eps + lane;
@@ -315,12 +334,13 @@ __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
     int32_t j_lane = load_j();
     if (planned) {
         const int32_t raw = lane < B ? sel_cnt[lane] : 0;
-        if (pr == 0 && h == 0 && wave == 0 && (raw < 0 || raw > k_max)) report(status, PULSE_ERR_BAD_INDEX);
+        if (piece == 0 && h == 0 && wave == 0 && (raw < 0 || raw > k_max)) report(status, PULSE_ERR_BAD_INDEX);
         p.cnt = k_max;
         p.nwg = sp.n_wg;
         if (!equal_counts(raw, B, k_max, lane)) {
             const int r0 = p.r, wg0 = p.wg;
-            p = plan_piece(pr, raw, B, k_max, Hkv, W, sp.eps, sp.n_wg, sp.step, sp.least, lane);
+            piece = (int)(blockIdx.z * gridDim.y + blockIdx.y);
+            p = plan_piece(piece, raw, B, k_max, W, sp, lane);
             if (p.r < 0) return;  // fewer pieces than workgroups
             if (p.r != r0 || p.wg != wg0 || p.eps != sp.eps) j_lane = load_j();
         }
@@ -363,7 +383,7 @@ __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
     }
     __syncthreads();
     // merge the W waves: thread handles outputs (g, c) = (idx / 128, idx % 128)
-    const size_t unit = (size_t)pr * Hkv + h;
+    const size_t unit = (size_t)piece * Hkv + h;
     for (int idx = tid; idx < G * kHeadDim; idx += kThreads) {
         const int g = idx / kHeadDim, c = idx % kHeadDim;
         float Mx = -INFINITY;
@@ -422,10 +442,10 @@ __global__ __launch_bounds__(kCombineThreads) void attn_combine_kernel(
         const int32_t raw = lane < B ? sel_cnt[lane] : 0;
         nwg = sp.n_wg;
         if (!equal_counts(raw, B, k_max, lane)) {
-            const Piece p = plan_piece(0, raw, B, k_max, Hkv, waves, sp.eps, sp.n_wg, sp.step, sp.least, lane);
+            const Piece p = plan_piece(0, raw, B, k_max, waves, sp, lane);
             // the request's own pieces: those of lane r
             const int cl = (raw >= 0 && raw <= k_max) ? raw : 0;
-            const uint32_t np = (uint32_t)pieces_of(cl, waves * p.eps);
+            const uint32_t np = (uint32_t)pieces_short(cl, waves * p.eps);
             nwg = __builtin_amdgcn_readlane((int)np, r);
             base = (int)last_lane(wave_scan(lane < r ? np : 0u, 0u, OpAdd()));
         }
@@ -513,13 +533,18 @@ hipError_t launch_attention(const pulse_shape& s, const void* q, const void* poo
     const AttnPlan p = attn_plan(B, Hkv, k_max, s.block_size);
     const int W = attn_waves(G);
     const int32_t n_wg = (p.n_split + W - 1) / W;
-    const dim3 grid((unsigned)Hkv, (unsigned)n_wg, (unsigned)B);
     SplitArgs sp;
     sp.eps = p.entries_per_split;
     sp.n_wg = n_wg;
     sp.step = split_step(s.block_size);
     sp.least = split_least(s.block_size);
-    sp.planned = n_wg > 1 && B <= kPlanRequests && k_max <= (1 << 24);  // the counts add up in 32 bits
+    const int64_t all = (int64_t)B * n_wg;
+    const int32_t round = PULSE_ATTN_TARGET_WAVES / (W * Hkv);  // pieces of one round
+    sp.fit = (int32_t)(4 * (int64_t)round >= 5 * (int64_t)B && round < all ? round : all);
+    sp.planned = n_wg > 1 && B <= kPlanRequests && (sp.eps >= 2 * sp.least || all > round) && k_max <= (1 << 22);
+    sp.light_last = p.n_split % W != 0 && all > round && n_wg <= 65535;
+    const dim3 grid = sp.light_last ? dim3((unsigned)Hkv, (unsigned)B, (unsigned)n_wg)
+                                    : dim3((unsigned)Hkv, (unsigned)n_wg, (unsigned)B);
     const size_t lds = sizeof(float) * W * G * kHeadDim + sizeof(float2) * W * G;
     const float scale_log2 = sm_scale * 1.4426950408889634f;
     // stop event of the split-K kernel: split_done, or `done` when no combine follows it

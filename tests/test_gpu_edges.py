@@ -219,6 +219,12 @@ PLAN_CASES = [
     ([1, 97, 98, 99, 513], 32, 8, 16, "bf16"), ([40] * 63 + [200], 2, 1, 16, "f16"),
     ([40] * 64 + [200], 2, 1, 16, "bf16"), ([7, 150, 33], 32, 2, 32, "bf16"), ([3, 260, 0, 31], 12, 1, 64, "f16"),
     ([0, 0], 4, 2, 16, "bf16"), ([9] * 40 + [800], 8, 8, 32, "bf16"),
+    # more than one round of workgroups whose last ones are light: equal counts, a host's split of one round and of
+    # more, no room for a plan of one round, more heads than a round has workgroups, 4-wave workgroups
+    ([129] * 12, 16, 8, 16, "bf16"), ([129] * 11 + [40], 16, 8, 16, "bf16"), ([129, 10, 3, 129] * 3, 16, 8, 16, "f16"),
+    ([60] * 31 + [250], 8, 8, 16, "bf16"), ([600, 5], 257, 257, 16, "f16"), ([300, 20, 77, 0, 150], 48, 4, 16, "bf16"),
+    ([700, 3, 41, 260, 0], 8, 8, 32, "bf16"), ([37, 1, 0, 12, 5, 9, 36], 8, 8, 64, "bf16"),
+    ([2900, 17, 1400], 8, 1, 16, "f16"),
 ]
 
 
