@@ -75,10 +75,10 @@ struct SplitArgs {
 // in registers), a plan up to the whole grid wherever counts differ, and as it is.  Over 560
 // calls drawn from 1 to 32 requests and budgets of 256 to 8192 tokens, lognormal or equal, the
 // second was 1.08 and this is 1.13 times as fast as the first; 101 and 11 calls lost over 1%.
-//   16 requests x 65K tokens, lognormal around 2048 tokens (188 MB)    58.0  42.7  43.0
-//   7 requests x 120K tokens, blocks of 32, around 2705 (100 MB)       29.4  31.0  23.7
-//   20 requests, 2 KV heads, all 387 blocks (280 workgroups)           34.6  39.0  29.6
-//   5 requests, 3 KV heads, around 702 tokens                          11.3  12.1  11.0
+//   16 requests x 65K tokens, lognormal around 2048 tokens (188 MB)    58.0  42.9  43.0
+//   7 requests x 120K tokens, blocks of 32, around 2705 (100 MB)       29.3  31.1  23.1
+//   20 requests, 2 KV heads, all 387 blocks (280 workgroups)           34.9  39.2  29.5
+//   5 requests, 3 KV heads, around 702 tokens                          11.3  12.1  10.9
 constexpr int kPlanRequests = 64;
 
 struct Piece {
@@ -300,9 +300,9 @@ __device__ inline void attend_split(const uint16_t* __restrict__ q, const uint16
     l_run = across_groups(l_run, [](float a, float b) { return a + b; });
 }
 
-// grid = (Hkv, n_wg, B), or (Hkv, B, n_wg) with light_last; in either, workgroup p is piece p / Hkv of KV head p % Hkv
-// of a plan; wave w of a request's workgroup wg owns split W * wg + w of eps entries.  Dynamic LDS: O [W][G][128] floats then
-// (m, l) [W][G] float2.
+// grid = (Hkv, n_wg, B), or (Hkv, B, n_wg) with light_last; in either, workgroup p is piece p / Hkv of KV head
+// p % Hkv of a plan; wave w of a request's workgroup wg owns split W * wg + w of eps entries.  Dynamic LDS:
+// O [W][G][128] floats then (m, l) [W][G] float2.
 template <int DT, int BS, int W>
 __global__ __launch_bounds__(W * kWave) void attn_splitk_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ pool, int32_t n_slots,
